@@ -33,13 +33,27 @@ static_assert(kTileC * kStageRows == kThreads && kTileC * kTileR == 2 * kThreads
               "a thread per staged output, two tile pixels per thread");
 
 // Largest shade of every slice (time bin) over the image: FP32 bits of
-// non-negative values compare as integers.
-__global__ void k_rs_slice_max(const int2* pix, long n, int R, int* smax)
+// non-negative values compare as integers.  Neighbouring pixels share few
+// slices, so global atomics serialise on their addresses (3.1 ms for 4096 x
+// 512 pixels); here a workgroup keeps the maxima of its
+// share of the pixels in LDS, where a plain read decides whether the atomic is
+// needed at all, and adds the slices it saw to the global maxima at the end.
+// Latency-bound then: 10 us (16.8 MB, 1.7 TB/s) for the same image.
+constexpr int kMaxGroups = 512;                // two workgroups per CU
+
+__global__ __launch_bounds__(kThreads)
+void k_rs_slice_max(const int2* pix, long n, int R, int* smax)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int2 rec = pix[i];
-    if (rec.x >= 0 && rec.x < R && rec.y > 0) atomicMax(smax + rec.x, rec.y);
+    extern __shared__ int lmax[];               // [R]
+    for (int i = threadIdx.x; i < R; i += kThreads) lmax[i] = 0;
+    __syncthreads();
+    for (long i = (long)blockIdx.x * kThreads + threadIdx.x; i < n; i += (long)gridDim.x * kThreads) {
+        const int2 rec = pix[i];
+        if (rec.x >= 0 && rec.x < R && rec.y > lmax[rec.x]) atomicMax(lmax + rec.x, rec.y);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < R; i += kThreads)
+        if (lmax[i] > 0) atomicMax(smax + i, lmax[i]);
 }
 
 __global__ void k_rs_clear(int* p, int n)
@@ -223,8 +237,9 @@ hipError_t launch_range_stacking(hipStream_t s, const RangeStackArgs& a, int* sm
     if (a.M > kMaxHalf || a.N > kMaxHalf || a.R > kMaxBins) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_rs_clear, dim3((a.R + 255) / 256), dim3(256), 0, s, smax_scratch, a.R);
     const long n = (long)a.W4 * a.H;
-    hipLaunchKernelGGL(k_rs_slice_max, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.pix, n,
-                       a.R, smax_scratch);
+    const long groups = (n + kThreads - 1) / kThreads;
+    hipLaunchKernelGGL(k_rs_slice_max, dim3((unsigned)(groups < kMaxGroups ? groups : kMaxGroups)), dim3(kThreads),
+                       sizeof(int) * (size_t)a.R, s, a.pix, n, a.R, smax_scratch);
     RangeStackArgs b = a;
     b.smax = smax_scratch;
     dim3 grid((a.W + kTileC - 1) / kTileC, (a.H + kTileR - 1) / kTileR);
