@@ -123,6 +123,20 @@ __device__ inline __attribute__((address_space(1))) T* gptr(T* p)
     return (__attribute__((address_space(1))) T*)p;
 }
 
+// Load of a read-only record at a uniform address through the scalar data
+// cache (constant address space): the record lands in scalar registers.
+template <typename T>
+__device__ inline T load_uniform(const T* p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole dwords");
+    struct Words { unsigned u[sizeof(T) / 4]; } w;
+    const __attribute__((address_space(4))) unsigned* q =
+        (const __attribute__((address_space(4))) unsigned*)p;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w.u[i] = q[i];
+    return __builtin_bit_cast(T, w);
+}
+
 // ---- per frame ----
 struct PrepassArgs {
     const float *depth, *refl, *gain, *nx, *ny, *nz;
@@ -291,20 +305,28 @@ bool footprint_group_fits(int G, int R, int J, size_t lds_max = 65536);
 
 // ---- range stacking (Alg. 2) with a separable kernel --------------------
 constexpr int kRsMaxHalf = 127;         // half extents M, N of the separable kernel
+constexpr int kRangeStackRows = 16;     // rows of an output tile
 struct RangeStackArgs {
     const int2* pix;            // pre-pass records [W4/4][H][4]
     int W, H, W4, R;
     const float* hk;            // [2M + 1] along the rows (columns m = -M..M)
-    const float* vk;            // [2N + 1] along the columns (rows n = -N..N)
+    const float* vk;            // [2N + 1] along the columns (rows n = -N..N), zero on
+                                // kRangeStackRows - 1 entries before and after
     int M, N;
     float rho_min;
     float bound;                // sum H * sum V (slice skipping)
     const int* smax;            // [R] largest shade per slice (FP32 bits)
+    int2* rows;                 // the records row by row, [H][W4] (workspace)
+    unsigned* present;          // bitmaps of the slices in every row's window (workspace)
     int32_t* s_nearest;         // [H][W]
     float* xi_nearest;          // [H][W]
 };
+// 32-bit words of the bitmap workspace (64 MB at most, unless the rows of one tile
+// need more)
+size_t range_stacking_map_words(int W, int H, int N, int R);
 // smax_scratch: [R] ints
-hipError_t launch_range_stacking(hipStream_t s, const RangeStackArgs& a, int* smax_scratch);
+hipError_t launch_range_stacking(hipStream_t s, const RangeStackArgs& a, int* smax_scratch, unsigned* map,
+                                 size_t map_words);
 
 // ---- reprojection of a pinhole rendering ---------------------------------
 struct ReprojectArgs {

@@ -157,20 +157,6 @@ __device__ inline float wave_total(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// Load of a read-only record at a uniform address through the scalar data
-// cache (constant address space): the record lands in scalar registers.
-template <typename T>
-__device__ inline T load_uniform(const T* p)
-{
-    static_assert(sizeof(T) % 4 == 0, "whole dwords");
-    struct Words { unsigned u[sizeof(T) / 4]; } w;
-    const __attribute__((address_space(4))) unsigned* q =
-        (const __attribute__((address_space(4))) unsigned*)p;
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w.u[i] = q[i];
-    return __builtin_bit_cast(T, w);
-}
-
 // An echo record stored field by field through a global-address-space
 // pointer (a global store: a flat one would also count against the LDS
 // counter, and the wave's next LDS wait would wait for it).

@@ -167,6 +167,8 @@ struct lidar_sim {
     std::vector<float> rs_host;
     uint32_t rs_M = ~0u, rs_N = ~0u;
     DevBuf<int> rs_smax;
+    DevBuf<int2> rs_rows;              // pixel records row by row
+    DevBuf<unsigned> rs_map;           // bitmaps of the slices in the image rows' windows
 
     // stats
     lidar_stats st{};
@@ -1811,7 +1813,9 @@ lidar_status lidar_sim_range_stacking(lidar_sim* h, const float* row_kernel, uin
         return fail(h, LIDAR_E_UNSUPPORTED, "range_stacking slices the pixels' centre ranges");
     const size_t KW = 2 * (size_t)M + 1, KH = 2 * (size_t)N + 1;
     double sh = 0.0, sv = 0.0;
-    std::vector<float> k(KW + KH);
+    // H, then V between zeros (the kernel reads V without bounds checks)
+    constexpr size_t kPad = kRangeStackRows - 1;
+    std::vector<float> k(KW + KH + 2 * kPad, 0.0f);
     for (size_t i = 0; i < KW; ++i) {
         if (!std::isfinite(row_kernel[i]) || row_kernel[i] < 0.0f)
             return fail(h, LIDAR_E_INVALID, "kernel factors must be finite and >= 0");
@@ -1821,7 +1825,7 @@ lidar_status lidar_sim_range_stacking(lidar_sim* h, const float* row_kernel, uin
     for (size_t i = 0; i < KH; ++i) {
         if (!std::isfinite(col_kernel[i]) || col_kernel[i] < 0.0f)
             return fail(h, LIDAR_E_INVALID, "kernel factors must be finite and >= 0");
-        k[KW + i] = col_kernel[i];
+        k[KW + kPad + i] = col_kernel[i];
         sv += col_kernel[i];
     }
     hipStream_t s = h->stream;
@@ -1852,15 +1856,21 @@ lidar_status lidar_sim_range_stacking(lidar_sim* h, const float* row_kernel, uin
     a.W4 = (int)((g.width + 3) & ~3u);
     a.R = (int)h->prm.n_bins;
     a.hk = h->rs_k.p;
-    a.vk = h->rs_k.p + KW;
+    a.vk = h->rs_k.p + KW + kPad;
     a.M = (int)M;
     a.N = (int)N;
     a.rho_min = (float)rho_min;
     a.bound = (float)(sh * sv);
     a.smax = nullptr;
+    a.rows = nullptr;
+    a.present = nullptr;
     a.s_nearest = s_nearest;
     a.xi_nearest = xi_nearest;
-    HIP_TRY(h, launch_range_stacking(s, a, h->rs_smax.p), "range stacking launch");
+    const size_t map_words = range_stacking_map_words(a.W, a.H, a.N, a.R);
+    HIP_TRY(h, h->rs_map.ensure(map_words), "allocate slice bitmaps");
+    HIP_TRY(h, h->rs_rows.ensure((size_t)a.W4 * a.H), "allocate row records");
+    a.rows = h->rs_rows.p;
+    HIP_TRY(h, launch_range_stacking(s, a, h->rs_smax.p, h->rs_map.p, map_words), "range stacking launch");
     return LIDAR_OK;
 }
 
