@@ -345,6 +345,22 @@ struct ReprojectArgs {
 };
 hipError_t launch_reproject(hipStream_t s, const ReprojectArgs& a);
 
+// ---- results into the caller's device arrays ------------------------------
+constexpr int kOutSegments = 4;         // echoes, counts, waveforms, beams
+struct OutSegment {
+    const void* src;
+    void* dst;
+    long bytes, blocks;         // blocks: workgroups of the segment
+    int unit, pad;              // bytes of an access: 16, 8 or 4
+};
+struct OutSegments {
+    OutSegment seg[kOutSegments];
+};
+// fills a segment; false when an address or the size is no multiple of 4
+bool out_segment(OutSegment* s, void* dst, const void* src, size_t bytes);
+// copies the segments (those with blocks = 0 are left out)
+hipError_t launch_copy_out(hipStream_t s, const OutSegments& a);
+
 // ---- host utility: a growable device buffer -----------------------------
 template <typename T>
 struct DevBuf {

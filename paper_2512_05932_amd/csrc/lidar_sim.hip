@@ -834,6 +834,53 @@ PathDev path_view(const lidar_sim* h)
     return p;
 }
 
+// ---- results -----------------------------------------------------------------
+
+// One array of a frame's results and where the caller wants it (null: not).
+struct Output {
+    void* dst;
+    const void* src;
+    size_t bytes;
+    const char* what;
+};
+
+// Whether [p, p + bytes) is memory of the current device inside one
+// allocation, which a kernel may write (anything else goes to the copy
+// engine, which checks its ranges and reaches other devices and the host).
+bool device_range(const void* p, size_t bytes)
+{
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    int dev = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
+        hipGetDevice(&dev) != hipSuccess || at.device != dev ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (size_t)((const char*)p - (const char*)base) + bytes <= size;
+}
+
+// The results into the caller's arrays: on the device one kernel on the
+// stream (arrays that it cannot take are copied one by one), to the host
+// copies and a synchronisation.
+lidar_status copy_outputs(lidar_sim* h, const Output (&out)[kOutSegments], bool device)
+{
+    hipStream_t s = h->stream;
+    OutSegments seg{};
+    for (int i = 0; i < kOutSegments; ++i) {
+        const Output& o = out[i];
+        if (!o.dst) continue;
+        if (device && device_range(o.dst, o.bytes) && out_segment(&seg.seg[i], o.dst, o.src, o.bytes)) continue;
+        HIP_TRY(h, hipMemcpyAsync(o.dst, o.src, o.bytes,
+                                  device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s), o.what);
+    }
+    HIP_TRY(h, launch_copy_out(s, seg), "copy results");
+    if (!device) HIP_TRY(h, hipStreamSynchronize(s), "read synchronise");
+    return LIDAR_OK;
+}
+
 // ---- surrogate inputs, gate, fallback ---------------------------------------
 
 // Cell sizes of the surrogate's inputs from the frame's kernel grid (host
@@ -2087,21 +2134,12 @@ lidar_status lidar_sim_read_echoes(lidar_sim* h, lidar_echo* echoes, int32_t* n_
     if (waveforms && !(h->prm.flags & LIDAR_KEEP_WAVEFORMS))
         return fail(h, LIDAR_E_INVALID, "waveforms requested without LIDAR_KEEP_WAVEFORMS");
     const size_t B = h->single.pat.az.size();
-    const hipMemcpyKind kind = dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    hipStream_t s = h->stream;
-    if (echoes)
-        HIP_TRY(h, hipMemcpyAsync(echoes, h->d_echoes.p, B * h->prm.max_echoes * sizeof(lidar_echo),
-                                  kind, s), "copy echoes");
-    if (n_echoes)
-        HIP_TRY(h, hipMemcpyAsync(n_echoes, h->d_counts.p, B * sizeof(int32_t), kind, s), "copy counts");
-    if (waveforms)
-        HIP_TRY(h, hipMemcpyAsync(waveforms, h->d_waves.p, B * (size_t)h->prm.n_bins * sizeof(float),
-                                  kind, s), "copy waveforms");
-    if (beams)
-        HIP_TRY(h, hipMemcpyAsync(beams, h->d_beams.p, B * sizeof(lidar_beam_info), kind, s),
-                "copy beam info");
-    if (!dst_is_device) HIP_TRY(h, hipStreamSynchronize(s), "read synchronise");
-    return LIDAR_OK;
+    const Output out[kOutSegments] = {
+        {echoes, h->d_echoes.p, B * h->prm.max_echoes * sizeof(lidar_echo), "copy echoes"},
+        {n_echoes, h->d_counts.p, B * sizeof(int32_t), "copy counts"},
+        {waveforms, h->d_waves.p, B * (size_t)h->prm.n_bins * sizeof(float), "copy waveforms"},
+        {beams, h->d_beams.p, B * sizeof(lidar_beam_info), "copy beam info"}};
+    return copy_outputs(h, out, dst_is_device != 0);
 }
 
 lidar_status lidar_sim_simulate_batch(lidar_sim* h, const lidar_gbuffer_desc* frames,
@@ -2148,21 +2186,12 @@ lidar_status lidar_sim_read_batch(lidar_sim* h, uint32_t frame, lidar_echo* echo
         return fail(h, LIDAR_E_INVALID, "waveforms requested without LIDAR_KEEP_WAVEFORMS");
     const uint64_t o = h->beam_off[frame], B = h->beam_off[frame + 1] - o;
     const size_t E = h->prm.max_echoes, R = h->prm.n_bins;
-    const hipMemcpyKind kind = dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    hipStream_t s = h->stream;
-    if (echoes)
-        HIP_TRY(h, hipMemcpyAsync(echoes, h->b_echoes.p + o * E, B * E * sizeof(lidar_echo), kind, s),
-                "copy echoes");
-    if (n_echoes)
-        HIP_TRY(h, hipMemcpyAsync(n_echoes, h->b_counts.p + o, B * sizeof(int32_t), kind, s), "copy counts");
-    if (waveforms)
-        HIP_TRY(h, hipMemcpyAsync(waveforms, h->b_waves.p + o * R, B * R * sizeof(float), kind, s),
-                "copy waveforms");
-    if (beams)
-        HIP_TRY(h, hipMemcpyAsync(beams, h->b_beams.p + o, B * sizeof(lidar_beam_info), kind, s),
-                "copy beam info");
-    if (!dst_is_device) HIP_TRY(h, hipStreamSynchronize(s), "read synchronise");
-    return LIDAR_OK;
+    const Output out[kOutSegments] = {
+        {echoes, h->b_echoes.p + o * E, B * E * sizeof(lidar_echo), "copy echoes"},
+        {n_echoes, h->b_counts.p + o, B * sizeof(int32_t), "copy counts"},
+        {waveforms, h->b_waves.p + o * R, B * R * sizeof(float), "copy waveforms"},
+        {beams, h->b_beams.p + o, B * sizeof(lidar_beam_info), "copy beam info"}};
+    return copy_outputs(h, out, dst_is_device != 0);
 }
 
 lidar_status lidar_sim_batch_info(lidar_sim* h, lidar_batch_info* out)
