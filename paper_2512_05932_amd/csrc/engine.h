@@ -435,12 +435,27 @@ struct BlasCtx;
 BlasCtx* blas_create();                 // null when the library cannot start
 void blas_destroy(BlasCtx* c);
 hipError_t blas_gemm(BlasCtx* c, hipStream_t s, const GemmArgs& g);
-hipError_t launch_bias_gelu(hipStream_t s, float* Z, const float* bias, uint16_t* H, long n, int C);
-hipError_t launch_bias(hipStream_t s, float* Y, const float* bias, long n, int C);
-hipError_t launch_loss(hipStream_t s, const float* Y, const float* lab, long n, uint16_t* dYb,
+// with `zero`, also clears zn floats there and the loss sum
+hipError_t launch_bias_gelu(hipStream_t s, const float* Z, const float* bias, uint16_t* H, long n, int C,
+                            float* zero = nullptr, long zn = 0, float* loss = nullptr);
+hipError_t launch_loss(hipStream_t s, const float* Y, const float* bias, const float* lab, long n, uint16_t* dYb,
                        float* loss_sum);
-hipError_t launch_gelu_back(hipStream_t s, const float* dH, const float* Z, uint16_t* dZb, long count);
-hipError_t launch_colsum(hipStream_t s, const uint16_t* D, long n, int C, float* out, bool det = false);
+hipError_t launch_gelu_back(hipStream_t s, const float* dH, const float* Z, const float* bias, uint16_t* dZb, long n,
+                            int C);
+// dW = A^T D and db = column sums of D for the four layers; a workgroup takes
+// `span` rows (span < n: added with atomics into zeroed gradients)
+struct WeightGradLayer {
+    const uint16_t *A, *D;              // [n][in], [n][out] BF16
+    int in, out, tiles;
+    float *dW, *db;                     // [in][out], [out]
+};
+struct WeightGradArgs {
+    WeightGradLayer layer[4];
+    long n, span;
+    int tiles;
+};
+long weight_grad_span(long n, bool det);
+hipError_t launch_weight_grads(hipStream_t s, const WeightGradArgs& a);
 hipError_t launch_zero_f32(hipStream_t s, float* p, long n);
 // minibatch rows perm_e(pos0 + i), i < b, of X [n][1056] BF16 and lab [n][16]
 // (perm_e: the seeded Feistel permutation of epoch e on values of 2 half bits)
@@ -570,7 +585,7 @@ struct SurNet {
 struct SurWork {                        // activations of up to `cap` rows
     long cap = 0;
     DevBuf<float> Z1, Z2, Z3, Y, dH, loss;
-    DevBuf<uint16_t> H1, H2, H3, dYb, dZb;
+    DevBuf<uint16_t> H1, H2, H3, dYb, dZ1, dZ2, dZ3;
     BlasCtx* blas = nullptr;            // library GEMMs of the training products (or null)
     bool blas_tried = false;
     hipError_t ensure(long n);
@@ -579,14 +594,16 @@ struct SurWork {                        // activations of up to `cap` rows
     SurWork& operator=(const SurWork&) = delete;
     ~SurWork() { blas_destroy(blas); }
 };
-// Y (w.Y, [n][16] FP32) of the rows X ([n][1056] BF16), keeping the
-// activations for the backward pass
-hipError_t sur_forward(hipStream_t s, const SurNet& net, const uint16_t* X, long n, SurWork& w);
+// Y (w.Y, [n][16] FP32, before the bias) of the rows X ([n][1056] BF16), keeping
+// the activations for the backward pass (Z before the biases); clears the loss
+// sum and the gradients (grad may be null)
+hipError_t sur_forward(hipStream_t s, const SurNet& net, const uint16_t* X, long n, SurWork& w, float* grad,
+                       float* loss);
 // Y ([n][16] FP32) of the rows X by the fused kernel (activations in LDS)
 hipError_t sur_infer(hipStream_t s, SurNet& net, const uint16_t* X, long n, float* Y);
-// loss (added into w.loss[0]) and parameter gradient (net.grad) of rows X
-// with labels lab ([n][16]); runs the forward pass first
+// loss [1] and parameter gradient grad [kSurParams] of rows X with labels lab
+// ([n][16]); runs the forward pass first
 hipError_t sur_gradients(hipStream_t s, SurNet& net, const uint16_t* X, const float* lab, long n,
-                         SurWork& w);
+                         SurWork& w, float* grad, float* loss);
 
 }  // namespace lidar

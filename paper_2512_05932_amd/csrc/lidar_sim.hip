@@ -2301,12 +2301,24 @@ lidar_status lidar_sim_surrogate_forward(lidar_sim* h, const void* x, float* y, 
     return LIDAR_OK;
 }
 
-static lidar_status sur_grads(lidar_sim* h, const void* x, const float* labels, uint32_t n)
+// Loss and gradients of the rows into `grads` and `loss`: by the kernels
+// themselves where these are device arrays that a kernel may write, else (or
+// null) into the handle's, from where they are copied.
+static lidar_status sur_grads(lidar_sim* h, const void* x, const float* labels, uint32_t n, float* grads, float* loss)
 {
     LIDAR_TRY(sur_check(h, x, labels, n));
-    HIP_TRY(h, launch_zero_f32(h->stream, h->work.loss.p, 1), "zero loss");
-    HIP_TRY(h, sur_gradients(h->stream, h->net, (const uint16_t*)x, labels, (long)n, h->work),
+    auto own = [](float* p, size_t count, float* ours) {
+        return p && (uintptr_t)p % sizeof(float) == 0 && device_range(p, count * sizeof(float)) ? p : ours;
+    };
+    const size_t P = (size_t)kSurParams;
+    float* g = own(grads, P, h->net.grad.p);
+    float* l = own(loss, 1, h->work.loss.p);
+    HIP_TRY(h, sur_gradients(h->stream, h->net, (const uint16_t*)x, labels, (long)n, h->work, g, l),
             "surrogate gradients");
+    if (grads && g != grads)
+        HIP_TRY(h, hipMemcpyAsync(grads, g, P * sizeof(float), hipMemcpyDeviceToDevice, h->stream), "copy gradients");
+    if (loss && l != loss)
+        HIP_TRY(h, hipMemcpyAsync(loss, l, sizeof(float), hipMemcpyDeviceToDevice, h->stream), "copy loss");
     return LIDAR_OK;
 }
 
@@ -2314,14 +2326,7 @@ lidar_status lidar_sim_surrogate_gradients(lidar_sim* h, const void* x, const fl
                                            uint32_t n, float* grads, float* loss)
 {
     if (!h) return LIDAR_E_INVALID;
-    LIDAR_TRY(sur_grads(h, x, labels, n));
-    if (grads)
-        HIP_TRY(h, hipMemcpyAsync(grads, h->net.grad.p, (size_t)kSurParams * sizeof(float),
-                                  hipMemcpyDeviceToDevice, h->stream), "copy gradients");
-    if (loss)
-        HIP_TRY(h, hipMemcpyAsync(loss, h->work.loss.p, sizeof(float), hipMemcpyDeviceToDevice,
-                                  h->stream), "copy loss");
-    return LIDAR_OK;
+    return sur_grads(h, x, labels, n, grads, loss);
 }
 
 static bool hparams_ok(const lidar_train_hparams* hp)
@@ -2336,7 +2341,7 @@ static bool hparams_ok(const lidar_train_hparams* hp)
 static lidar_status adam_step(lidar_sim* h, const void* x, const float* labels, uint32_t n,
                               const lidar_train_hparams* hp, double lr, float* loss)
 {
-    LIDAR_TRY(sur_grads(h, x, labels, n));
+    LIDAR_TRY(sur_grads(h, x, labels, n, nullptr, loss));
     SurNet& net = h->net;
     const long t = ++net.step;
     AdamArgs a;
@@ -2350,9 +2355,6 @@ static lidar_status adam_step(lidar_sim* h, const void* x, const float* labels, 
     HIP_TRY(h, launch_adamw(h->stream, net.theta.p, net.grad.p, net.m.p, net.v.p, net.theta_b.p,
                             kSurParams, a), "AdamW launch");
     net.t_stale = true;
-    if (loss)
-        HIP_TRY(h, hipMemcpyAsync(loss, h->work.loss.p, sizeof(float), hipMemcpyDeviceToDevice,
-                                  h->stream), "copy loss");
     return LIDAR_OK;
 }
 

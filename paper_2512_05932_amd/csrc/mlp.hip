@@ -6,6 +6,8 @@
 // 13..15 are padding), GELU(z) = z/2 (1 + erf(z / sqrt 2)).  Weights are
 // kept in FP32 (the optimiser's copy) and in BF16 (the operands of the
 // products); activations between layers and the backward operands are BF16.
+#include <algorithm>
+
 #include "engine.h"
 
 namespace lidar {
@@ -14,6 +16,8 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16v4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTileM = 64, kTileN = 64, kTileK = 32;
 constexpr int kLdsK = kTileK + 8;         // row stride in LDS (elements)
@@ -126,35 +130,39 @@ __device__ inline float gelu_prime(float z)
            z * __expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// Z += bias (in place); H = bf16(gelu(Z)).
-__global__ void k_bias_gelu(float* Z, const float* bias, uint16_t* H, long n, int C)
+// H = bf16(gelu(Z + bias)), four elements a thread (C a multiple of 4); with
+// `zero`, also clears zn floats there and the loss sum (the first layer does,
+// ahead of the kernels that add into them: a launch for each was 4.4 us).
+__global__ __launch_bounds__(256)
+void k_bias_gelu(const float4* Z, const float4* bias, bf16x4* H, long n4, int C4, float* zero, long zn, float* loss)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * C) return;
-    const float z = Z[i] + bias[i % C];
-    Z[i] = z;
-    H[i] = to_bf16(gelu(z));
-}
-
-__global__ void k_bias(float* Y, const float* bias, long n, int C)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * C) return;
-    Y[i] += bias[i % C];
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (zero) {
+        for (long k = i; k < zn; k += (long)gridDim.x * 256) zero[k] = 0.0f;
+        if (i == 0) *loss = 0.0f;
+    }
+    if (i >= n4) return;
+    const float4 z = Z[i], b = bias[i % C4];
+    H[i] = bf16x4{(short)to_bf16(gelu(z.x + b.x)), (short)to_bf16(gelu(z.y + b.y)), (short)to_bf16(gelu(z.z + b.z)),
+                  (short)to_bf16(gelu(z.w + b.w))};
 }
 
 __device__ inline float bce(float z, float t) { return fmaxf(z, 0.0f) - z * t + log1pf(expf(-fabsf(z))); }
 __device__ inline float sigm(float z) { return 1.0f / (1.0f + expf(-z)); }
 
-// Per-row loss and gradient (scaled by 1/n) with respect to the 16 outputs.
-__global__ void k_loss(const float* Y, const float* lab, long n, float inv_n, uint16_t* dYb,
-                       float* loss_sum)
+// Per-row loss and gradient (scaled by 1/n) with respect to the 16 outputs Y +
+// bias; a wave per 64 rows (4096 rows then take 64 CUs and not 16: 7 us of
+// dependent exponentials and logarithms become 5).
+__global__ __launch_bounds__(64)
+void k_loss(const float* Y, const float* bias, const float* lab, long n, float inv_n, uint16_t* dYb, float* loss_sum)
 {
-    const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long r = (long)blockIdx.x * 64 + threadIdx.x;
     float L = 0.0f;
     if (r < n) {
-        const float* y = Y + r * 16;
         const float* l = lab + r * 16;
+        float y[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) y[j] = Y[r * 16 + j] + bias[j];
         float d[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) d[j] = 0.0f;
@@ -182,41 +190,147 @@ __global__ void k_loss(const float* Y, const float* lab, long n, float inv_n, ui
 #pragma unroll
         for (int j = 0; j < 16; ++j) dYb[r * 16 + j] = to_bf16(d[j] * inv_n);
     }
-    // block sum of the row losses, one atomic per block
-    __shared__ float part[256];
-    part[threadIdx.x] = L;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
+    // the wave's sum of the row losses, one atomic
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) L += __shfl_xor(L, m);
+    if (threadIdx.x == 0) atomicAdd(loss_sum, L * inv_n);
+}
+
+// dZ = bf16(dH * gelu'(Z + bias)), four elements a thread
+__global__ __launch_bounds__(256)
+void k_gelu_back(const float4* dH, const float4* Z, const float4* bias, bf16x4* dZb, long n4, int C4)
+{
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const float4 d = dH[i], z = Z[i], b = bias[i % C4];
+    dZb[i] = bf16x4{(short)to_bf16(d.x * gelu_prime(z.x + b.x)), (short)to_bf16(d.y * gelu_prime(z.y + b.y)),
+                    (short)to_bf16(d.z * gelu_prime(z.z + b.z)), (short)to_bf16(d.w * gelu_prime(z.w + b.w))};
+}
+
+// Weight and bias gradients of all layers in one launch: dW = A^T D (A
+// [n][in] BF16 activations, D [n][out] BF16 output gradients), db = column
+// sums of D, FP32 accumulation on the MFMA units.
+//
+// The products are small (256 x 256 and 1056 x 256 outputs) with a long sum over
+// the n rows, so the rows are split over the grid as well: a workgroup takes a
+// kGradT x kGradT tile of one layer over `span` rows and adds it to dW (zeroed
+// before) with atomics, or stores it when span covers every row (then the
+// order of the sum is fixed).  Both operands have the rows outermost, while
+// an MFMA fragment holds eight consecutive rows of a column: a thread loads
+// four rows of eight columns, turns them in registers and writes four-row
+// pieces into a [column][row] tile in LDS, from where a fragment is one
+// 16-byte read; the next step's rows are loaded meanwhile.
+// A library product per layer with 16 to 68 workgroups, and the column sums
+// apart, took 28 us and 16 us each (4096 rows); all four layers here 19 us,
+// bound by the latency of the loads (without the atomics it takes as long).
+constexpr int kGradT = 64;                   // tile of dW: in x out
+constexpr int kGradK = 64;                   // rows per step
+constexpr int kGradLd = kGradK + 8;          // row stride of an LDS tile (elements)
+
+__global__ __launch_bounds__(256) void k_weight_grads(WeightGradArgs a)
+{
+    __shared__ __align__(16) uint16_t tile[2][kGradT][kGradLd];    // A, D: [column][row]
+    __shared__ float part[2][kGradT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // this workgroup's layer and tile
+    int t = blockIdx.x % a.tiles, l = 0;
+    const long r0 = (long)(blockIdx.x / a.tiles) * a.span, r1 = min(a.n, r0 + a.span);
+    while (t >= a.layer[l].tiles) t -= a.layer[l++].tiles;
+    const WeightGradLayer g = a.layer[l];
+    const int tiles_out = (g.out + kGradT - 1) / kGradT;
+    const int i0 = t / tiles_out * kGradT, j0 = t % tiles_out * kGradT;
+    const bool atomic = a.span < a.n;
+    // operand (0: A, 1: D), columns 8 cb .. and rows 4 rq .. of this thread
+    const int op = wave >> 1, cb = tid & 7, rq = (tid & 127) >> 3;
+    const uint16_t* src = op ? g.D : g.A;
+    const int ld = op ? g.out : g.in, c = (op ? j0 : i0) + 8 * cb;
+    const bool col_ok = c < ld;                      // in and out are multiples of 8
+    const bool sums = op == 1 && i0 == 0;            // the column sums of D, once per column
+    float cs[8] = {};
+    uint4 q[4];
+    auto load = [&](long r) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const long row = r + 4 * rq + k;
+            q[k] = col_ok && row < r1 ? *(const uint4*)(src + row * ld + c) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    };
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, quad = lane >> 4;
+    load(r0);
+    for (long r = r0; r < r1; r += kGradK) {
+        __syncthreads();                             // the last step's fragments are read
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const unsigned x[4] = {(&q[0].x)[w], (&q[1].x)[w], (&q[2].x)[w], (&q[3].x)[w]};
+            // columns 2 w and 2 w + 1: their four rows
+            const uint2 lo = make_uint2(__builtin_amdgcn_perm(x[1], x[0], 0x05040100u),
+                                        __builtin_amdgcn_perm(x[3], x[2], 0x05040100u));
+            const uint2 hi = make_uint2(__builtin_amdgcn_perm(x[1], x[0], 0x07060302u),
+                                        __builtin_amdgcn_perm(x[3], x[2], 0x07060302u));
+            *(uint2*)&tile[op][8 * cb + 2 * w][4 * rq] = lo;
+            *(uint2*)&tile[op][8 * cb + 2 * w + 1][4 * rq] = hi;
+            if (sums) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    cs[2 * w] += __uint_as_float(x[k] << 16);
+                    cs[2 * w + 1] += __uint_as_float(x[k] & 0xffff0000u);
+                }
+            }
+        }
         __syncthreads();
+        if (r + kGradK < r1) load(r + kGradK);
+#pragma unroll
+        for (int k = 0; k < kGradK; k += 32) {
+            bf16x8 fa[2], fb[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                fa[i] = *(const bf16x8*)&tile[0][wm * 32 + i * 16 + l16][k + 8 * quad];
+                fb[i] = *(const bf16x8*)&tile[1][wn * 32 + i * 16 + l16][k + 8 * quad];
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        }
     }
-    if (threadIdx.x == 0 && loss_sum) atomicAdd(loss_sum, part[0] * inv_n);
-}
-
-// dZ = bf16(dH * gelu'(Z))
-__global__ void k_gelu_back(const float* dH, const float* Z, uint16_t* dZb, long count)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    dZb[i] = to_bf16(dH[i] * gelu_prime(Z[i]));
-}
-
-// db[j] += sum over rows of the BF16 operand dZ[r][j]: a workgroup takes 64
-// columns x `span` rows (lane = column, wave = every 4th row), sums its waves
-// in LDS and adds into the zeroed output (one workgroup per column block
-// when span covers every row: then the sum has a fixed order)
-__global__ __launch_bounds__(256) void k_colsum(const uint16_t* D, long n, int C, long span, float* out)
-{
-    __shared__ float part[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + lane;
-    const long r0 = (long)blockIdx.y * span;
-    float s = 0.0f;
-    if (j < C)
-        for (long r = r0 + wave; r < min(n, r0 + span); r += 4) s += from_bf16(D[r * C + j]);
-    part[wave][lane] = s;
+    // lane: column l16, rows 4 quad + r of every 16 x 16 block
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int col = j0 + wn * 32 + j * 16 + l16;
+            if (col >= g.out) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int row = i0 + wm * 32 + i * 16 + 4 * quad + k;
+                if (row >= g.in) continue;
+                float* p = g.dW + (long)row * g.out + col;
+                if (atomic) unsafeAtomicAdd(p, acc[i][j][k]);
+                else *p = acc[i][j][k];
+            }
+        }
+    if (i0 != 0) return;                             // the whole workgroup
+    // column sums: over the lanes of a column block, then the two waves
+    if (op == 1) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            float v = cs[k];
+            for (int m = 8; m < 64; m <<= 1) v += __shfl_xor(v, m);
+            if (lane < 8) part[wave & 1][8 * cb + k] = v;
+        }
+    }
     __syncthreads();
-    if (wave == 0 && j < C) atomicAdd(&out[j], part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane]);
+    if (tid < kGradT && j0 + tid < g.out) {
+        const float v = part[0][tid] + part[1][tid];
+        if (atomic) unsafeAtomicAdd(g.db + j0 + tid, v);
+        else g.db[j0 + tid] = v;
+    }
 }
 
 __global__ void k_zero_f32(float* p, long n)
@@ -305,9 +419,6 @@ __global__ void k_transpose_bf16(const uint16_t* W, int in, int out, uint16_t* W
     const int k = (int)(i / out), n = (int)(i % out);
     Wt[(long)n * in + k] = W[i];
 }
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16v4 __attribute__((ext_vector_type(4)));
 
 // Fused inference with the activations in registers.  The weights are the
 // MFMA's A operand (a tile of 16 output features) and the beams its B operand
@@ -519,43 +630,59 @@ hipError_t launch_gemm_bf16(hipStream_t s, const GemmArgs& g0, bool det)
     return hipGetLastError();
 }
 
-hipError_t launch_bias_gelu(hipStream_t s, float* Z, const float* bias, uint16_t* H, long n, int C)
+hipError_t launch_bias_gelu(hipStream_t s, const float* Z, const float* bias, uint16_t* H, long n, int C,
+                            float* zero, long zn, float* loss)
 {
     if (n * C == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(n * C, 256)), dim3(256), 0, s, Z, bias, H, n, C);
+    if (C % 4 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(n * C / 4, 256)), dim3(256), 0, s, (const float4*)Z,
+                       (const float4*)bias, (bf16x4*)H, n * C / 4, C / 4, zero, zn, loss);
     return hipGetLastError();
 }
 
-hipError_t launch_bias(hipStream_t s, float* Y, const float* bias, long n, int C)
-{
-    if (n * C == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bias, dim3(blocks(n * C, 256)), dim3(256), 0, s, Y, bias, n, C);
-    return hipGetLastError();
-}
-
-hipError_t launch_loss(hipStream_t s, const float* Y, const float* lab, long n, uint16_t* dYb,
+hipError_t launch_loss(hipStream_t s, const float* Y, const float* bias, const float* lab, long n, uint16_t* dYb,
                        float* loss_sum)
 {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_loss, dim3(blocks(n, 256)), dim3(256), 0, s, Y, lab, n, 1.0f / (float)n,
-                       dYb, loss_sum);
+    hipLaunchKernelGGL(k_loss, dim3(blocks(n, 64)), dim3(64), 0, s, Y, bias, lab, n, 1.0f / (float)n, dYb,
+                       loss_sum);
     return hipGetLastError();
 }
 
-hipError_t launch_gelu_back(hipStream_t s, const float* dH, const float* Z, uint16_t* dZb, long count)
+hipError_t launch_gelu_back(hipStream_t s, const float* dH, const float* Z, const float* bias, uint16_t* dZb, long n,
+                            int C)
 {
-    if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gelu_back, dim3(blocks(count, 256)), dim3(256), 0, s, dH, Z, dZb, count);
+    if (n * C == 0) return hipSuccess;
+    if (C % 4 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gelu_back, dim3(blocks(n * C / 4, 256)), dim3(256), 0, s, (const float4*)dH,
+                       (const float4*)Z, (const float4*)bias, (bf16x4*)dZb, n * C / 4, C / 4);
     return hipGetLastError();
 }
 
-hipError_t launch_colsum(hipStream_t s, const uint16_t* D, long n, int C, float* out, bool det)
+// Rows of a workgroup: all of them when the sum's order is to be fixed (det)
+// or the rows are few, else shares of at least 256 rows, at most 64 of them (a
+// step on 4096 rows: 116 us with shares of 512 rows, too few workgroups to
+// hide their loads; 110 us with 256; 134 us with 128, where the atomics cost
+// more).
+long weight_grad_span(long n, bool det)
 {
-    hipError_t e = launch_zero_f32(s, out, C);
-    if (e != hipSuccess || n == 0) return e;
-    const long span = det ? n : 256;
-    hipLaunchKernelGGL(k_colsum, dim3(blocks(C, 64), (unsigned)((n + span - 1) / span)), dim3(256), 0, s,
-                       D, n, C, span, out);
+    if (det || n <= 256) return n;
+    const long parts = std::min<long>(64, (n + 255) / 256);
+    return ((n + parts - 1) / parts + kGradK - 1) / kGradK * kGradK;
+}
+
+hipError_t launch_weight_grads(hipStream_t s, const WeightGradArgs& a0)
+{
+    if (a0.n <= 0) return hipSuccess;
+    WeightGradArgs a = a0;
+    a.tiles = 0;
+    for (WeightGradLayer& l : a.layer) {
+        if (l.in % 8 != 0 || l.out % 8 != 0) return hipErrorInvalidValue;
+        l.tiles = ((l.in + kGradT - 1) / kGradT) * ((l.out + kGradT - 1) / kGradT);
+        a.tiles += l.tiles;
+    }
+    const long parts = (a.n + a.span - 1) / a.span;
+    hipLaunchKernelGGL(k_weight_grads, dim3((unsigned)(a.tiles * parts)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -600,8 +727,9 @@ hipError_t SurWork::ensure(long n)
     hipError_t e;
     const size_t nh = (size_t)n * kSurHid, no = (size_t)n * kSurOut;
     if ((e = Z1.ensure(nh)) || (e = Z2.ensure(nh)) || (e = Z3.ensure(nh)) || (e = dH.ensure(nh)) ||
-        (e = H1.ensure(nh)) || (e = H2.ensure(nh)) || (e = H3.ensure(nh)) || (e = dZb.ensure(nh)) ||
-        (e = Y.ensure(no)) || (e = dYb.ensure(no)) || (e = loss.ensure(1)))
+        (e = H1.ensure(nh)) || (e = H2.ensure(nh)) || (e = H3.ensure(nh)) || (e = dZ1.ensure(nh)) ||
+        (e = dZ2.ensure(nh)) || (e = dZ3.ensure(nh)) || (e = Y.ensure(no)) || (e = dYb.ensure(no)) ||
+        (e = loss.ensure(1)))
         return e;
     cap = n;
     return hipSuccess;
@@ -633,19 +761,19 @@ static hipError_t dense(hipStream_t s, const uint16_t* A, int k, const uint16_t*
     return gemm(s, g, det, blas);
 }
 
-hipError_t sur_forward(hipStream_t s, const SurNet& net, const uint16_t* X, long n, SurWork& w)
+hipError_t sur_forward(hipStream_t s, const SurNet& net, const uint16_t* X, long n, SurWork& w, float* grad,
+                       float* loss)
 {
     const uint16_t* Wb = net.theta_b.p;
     const float* th = net.theta.p;
     TRY(dense(s, X, kSurIn, Wb + kSurOffW1, kSurHid, n, w.Z1.p, net.det, w.blas));
-    TRY(launch_bias_gelu(s, w.Z1.p, th + kSurOffB1, w.H1.p, n, kSurHid));
+    TRY(launch_bias_gelu(s, w.Z1.p, th + kSurOffB1, w.H1.p, n, kSurHid, grad ? grad : loss,
+                         grad ? kSurParams : 0, loss));
     TRY(dense(s, w.H1.p, kSurHid, Wb + kSurOffW2, kSurHid, n, w.Z2.p, net.det, w.blas));
     TRY(launch_bias_gelu(s, w.Z2.p, th + kSurOffB2, w.H2.p, n, kSurHid));
     TRY(dense(s, w.H2.p, kSurHid, Wb + kSurOffW3, kSurHid, n, w.Z3.p, net.det, w.blas));
     TRY(launch_bias_gelu(s, w.Z3.p, th + kSurOffB3, w.H3.p, n, kSurHid));
-    TRY(dense(s, w.H3.p, kSurHid, Wb + kSurOffW4, kSurOut, n, w.Y.p, net.det, w.blas));
-    TRY(launch_bias(s, w.Y.p, th + kSurOffB4, n, kSurOut));
-    return hipSuccess;
+    return dense(s, w.H3.p, kSurHid, Wb + kSurOffW4, kSurOut, n, w.Y.p, net.det, w.blas);
 }
 
 hipError_t sur_infer(hipStream_t s, SurNet& net, const uint16_t* X, long n, float* Y)
@@ -671,15 +799,6 @@ hipError_t sur_infer(hipStream_t s, SurNet& net, const uint16_t* X, long n, floa
     return launch_mlp_infer(s, a);
 }
 
-// dW = A^T D (A [n][in] BF16 activations, D [n][out] BF16), db = column sums
-static hipError_t weight_grad(hipStream_t s, const uint16_t* A, int in, const uint16_t* D, int out,
-                              long n, float* dW, float* db, bool det, BlasCtx* blas)
-{
-    GemmArgs g{A, 1, in, D, out, 1, dW, out, in, out, (int)n, 1};
-    TRY(gemm(s, g, det, blas));
-    return launch_colsum(s, D, n, out, db, det);
-}
-
 // dH = D W^T (D [n][out], W [in][out]) in FP32
 static hipError_t input_grad(hipStream_t s, const uint16_t* D, int out, const uint16_t* W, int in,
                              long n, float* dH, bool det, BlasCtx* blas)
@@ -689,28 +808,27 @@ static hipError_t input_grad(hipStream_t s, const uint16_t* D, int out, const ui
 }
 
 hipError_t sur_gradients(hipStream_t s, SurNet& net, const uint16_t* X, const float* lab, long n,
-                         SurWork& w)
+                         SurWork& w, float* g, float* loss)
 {
-    TRY(sur_forward(s, net, X, n, w));
-    TRY(launch_loss(s, w.Y.p, lab, n, w.dYb.p, w.loss.p));
     const uint16_t* Wb = net.theta_b.p;
-    float* g = net.grad.p;
-    const long nh = n * kSurHid;
-    // layer 4
-    TRY(weight_grad(s, w.H3.p, kSurHid, w.dYb.p, kSurOut, n, g + kSurOffW4, g + kSurOffB4, net.det, w.blas));
+    const float* th = net.theta.p;
+    const long span = weight_grad_span(n, net.det);
+    TRY(sur_forward(s, net, X, n, w, span < n ? g : nullptr, loss));
+    TRY(launch_loss(s, w.Y.p, th + kSurOffB4, lab, n, w.dYb.p, loss));
     TRY(input_grad(s, w.dYb.p, kSurOut, Wb + kSurOffW4, kSurHid, n, w.dH.p, net.det, w.blas));
-    TRY(launch_gelu_back(s, w.dH.p, w.Z3.p, w.dZb.p, nh));
-    // layer 3
-    TRY(weight_grad(s, w.H2.p, kSurHid, w.dZb.p, kSurHid, n, g + kSurOffW3, g + kSurOffB3, net.det, w.blas));
-    TRY(input_grad(s, w.dZb.p, kSurHid, Wb + kSurOffW3, kSurHid, n, w.dH.p, net.det, w.blas));
-    TRY(launch_gelu_back(s, w.dH.p, w.Z2.p, w.dZb.p, nh));
-    // layer 2
-    TRY(weight_grad(s, w.H1.p, kSurHid, w.dZb.p, kSurHid, n, g + kSurOffW2, g + kSurOffB2, net.det, w.blas));
-    TRY(input_grad(s, w.dZb.p, kSurHid, Wb + kSurOffW2, kSurHid, n, w.dH.p, net.det, w.blas));
-    TRY(launch_gelu_back(s, w.dH.p, w.Z1.p, w.dZb.p, nh));
-    // layer 1
-    TRY(weight_grad(s, X, kSurIn, w.dZb.p, kSurHid, n, g + kSurOffW1, g + kSurOffB1, net.det, w.blas));
-    return hipSuccess;
+    TRY(launch_gelu_back(s, w.dH.p, w.Z3.p, th + kSurOffB3, w.dZ3.p, n, kSurHid));
+    TRY(input_grad(s, w.dZ3.p, kSurHid, Wb + kSurOffW3, kSurHid, n, w.dH.p, net.det, w.blas));
+    TRY(launch_gelu_back(s, w.dH.p, w.Z2.p, th + kSurOffB2, w.dZ2.p, n, kSurHid));
+    TRY(input_grad(s, w.dZ2.p, kSurHid, Wb + kSurOffW2, kSurHid, n, w.dH.p, net.det, w.blas));
+    TRY(launch_gelu_back(s, w.dH.p, w.Z1.p, th + kSurOffB1, w.dZ1.p, n, kSurHid));
+    WeightGradArgs a{};
+    a.n = n;
+    a.span = span;
+    a.layer[0] = {X, w.dZ1.p, kSurIn, kSurHid, 0, g + kSurOffW1, g + kSurOffB1};
+    a.layer[1] = {w.H1.p, w.dZ2.p, kSurHid, kSurHid, 0, g + kSurOffW2, g + kSurOffB2};
+    a.layer[2] = {w.H2.p, w.dZ3.p, kSurHid, kSurHid, 0, g + kSurOffW3, g + kSurOffB3};
+    a.layer[3] = {w.H3.p, w.dYb.p, kSurHid, kSurOut, 0, g + kSurOffW4, g + kSurOffB4};
+    return launch_weight_grads(s, a);
 }
 
 #undef TRY
