@@ -266,15 +266,20 @@ struct BatchArgs {
     const int32_t* groups;      // [total groups][G]: each frame's groups, concatenated
     const int2* items;          // [n_items] {frame, global group index}, costliest first
     int n_items, G;
-    int* next_item;             // work-queue counter(s), zeroed by k_reset_queue: with tickets
-                                // kXcds counters kQueueStride ints apart, else one
+    int* next_item;             // work-queue counters, zeroed by k_reset_queue: kXcds of
+                                // them kQueueStride ints apart
     const int* n_items_dev;     // if set: the item count, read on the device
-    // if set: the queue hands out tickets, ticket t = items [tickets[t],
-    // tickets[t + 1]) (non-empty); else one item per queue step
+    // if set: ticket t = items [tickets[t], tickets[t + 1]) (non-empty); else
+    // ticket t is item t
     const int* tickets;         // [n_tickets + 1]
     int n_tickets;
     int* fcount;                // {beams in fixed point, beams run again in FP32} (or null)
 };
+// Workgroups per CU that the wave schedule's kernel keeps resident.  A wave's
+// first ticket is its own number, so the grid must not exceed them: a
+// workgroup that starts when another has left would hold its costly first
+// tickets until then.
+int footprint_wave_resident(int R, int J, bool sun, bool keep);
 hipError_t launch_footprint_batch(hipStream_t s, const BatchArgs& a, int grid, bool sun,
                                   bool keep);
 // the wave schedule over the tickets of a (kWavesPerGroup beams per group,

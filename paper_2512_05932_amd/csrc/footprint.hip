@@ -1571,20 +1571,21 @@ void k_sun_floor(SunFloorArgs a)
     }
 }
 
-// Next ticket from the dispenser of a batch: kXcds counters kQueueStride ints
-// apart, counter c handing out tickets c, c + kXcds, ... (so the costliest
-// tickets still go first).  A worker starts at its XCD's counter and moves to
-// the next one when it runs dry; the atomics of the workers are spread over
-// eight addresses instead of serialising on one, and a counter seen dry by a
-// plain load is passed over without an atomic.  Returns n when every counter
-// is exhausted.
-__device__ inline int next_ticket(int* q, int& c, int n)
+// Next ticket, from number `first` on, from the dispenser of a batch: kXcds
+// counters kQueueStride ints apart, counter c handing out tickets first + c,
+// first + c + kXcds, ... (so the costliest tickets still go first).  A worker
+// starts at its XCD's counter and moves to the next one when it runs dry; the
+// atomics of the workers are spread over eight addresses instead of
+// serialising on one, and a counter seen dry by a plain load is passed over
+// without an atomic.  Returns n when every counter is exhausted.
+__device__ inline int next_ticket(int* q, int& c, int first, int n)
 {
+    if (first >= n) return n;
     for (int tried = 0; tried < kXcds; ++tried) {
         int* qc = q + c * kQueueStride;
         if (tried == 0 ||
-            __hip_atomic_load(qc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * kXcds + c < n) {
-            const int t = atomicAdd(qc, 1) * kXcds + c;
+            first + __hip_atomic_load(qc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * kXcds + c < n) {
+            const int t = first + atomicAdd(qc, 1) * kXcds + c;
             if (t < n) return t;
         }
         c = c + 1 == kXcds ? 0 : c + 1;
@@ -1611,6 +1612,7 @@ void k_footprint_batch(BatchArgs a)
     __shared__ int item_sh;
     const int tid = threadIdx.x;
     load_taps(taps, a.p.taps, a.p.J, tid);
+    // without tickets, ticket t is item t
     const int n_tickets = a.tickets ? a.n_tickets : (a.n_items_dev ? *a.n_items_dev : a.n_items);
     int qc = blockIdx.x % kXcds;                         // this workgroup's XCD (round-robin dispatch)
     // this wave's counts {beams in fixed point, beams run again}, added to the
@@ -1620,7 +1622,7 @@ void k_footprint_batch(BatchArgs a)
     const int wave = tid >> 6;
     if ((tid & 63) < 2) fxn[wave][tid & 63] = 0;
     for (;;) {
-        if (tid == 0) item_sh = a.tickets ? next_ticket(a.next_item, qc, n_tickets) : atomicAdd(a.next_item, 1);
+        if (tid == 0) item_sh = next_ticket(a.next_item, qc, 0, n_tickets);
         clear_group(lds4, G * RS / 4, &nzmask, tid);
         __syncthreads();
         const int t = __builtin_amdgcn_readfirstlane(item_sh);
@@ -1655,10 +1657,14 @@ void k_footprint_batch(BatchArgs a)
 
 // Wave schedule of a batch (frames whose groups are mostly single beams with
 // small footprints, where three of the four waves of a group would idle):
-// every wave of the persistent workgroups takes tickets from its own queue
-// counter and processes the items' beams one by one in its own histogram slot,
+// every wave of the persistent workgroups begins with the ticket of its own
+// number, goes on with tickets from the queue and processes the items' beams one by one in its own histogram slot,
 // with no workgroup barrier after the taps are loaded; the workgroup's LDS is
 // that of a group of kWaves beams.  Every wave exits once its queue is empty.
+// A small batch has a ticket or none for a wave, and then asks no counter: with
+// every ticket from the counters, 8000 beams of 89 samples (8 frames, 512
+// bins) on 8192 waves took 72 us, most of it in serialised atomics; 64 us in
+// tickets of four beams, which left three of four waves idle; 26 us now.
 template <int NP, bool SUN, bool KEEP>
 __global__ __launch_bounds__(kFootprintThreads) __attribute__((amdgpu_waves_per_eu(KEEP || SUN ? 1 : (NP == 1 ? 8 : 4))))
 void k_footprint_batch_wave(BatchArgs a)
@@ -1684,11 +1690,13 @@ void k_footprint_batch_wave(BatchArgs a)
     __shared__ int fxn[kWaves][2];
     if (lane < 2) fxn[wave][lane] = 0;
     int left = 0;                                        // what the last beam left in the slot
-    for (;;) {
-        int t = 0;
-        if (lane == 0) t = next_ticket(a.next_item, qc, a.n_tickets);
-        t = __builtin_amdgcn_readlane(t, 0);
-        if (t >= a.n_tickets) break;                     // uniform over the wave
+    for (bool first = true;; first = false) {
+        int t = blockIdx.x * kWaves + wave;              // uniform over the wave
+        if (!first) {
+            if (lane == 0) t = next_ticket(a.next_item, qc, gridDim.x * kWaves, a.n_tickets);
+            t = __builtin_amdgcn_readlane(t, 0);
+        }
+        if (t >= a.n_tickets) break;
         const int i0 = load_uniform(a.tickets + t), i1 = load_uniform(a.tickets + t + 1);
         for (int item = i0; item < i1; ++item) {
             const int2 it = load_uniform(a.items + item);
@@ -1740,19 +1748,43 @@ static hipError_t launch_g(hipStream_t s, const FootprintArgs& a)
     return hipGetLastError();
 }
 
+using BatchKernel = void (*)(BatchArgs);
+
 template <int G>
-static hipError_t launch_batch_g(hipStream_t s, const BatchArgs& a, int grid, bool sun, bool keep)
+static BatchKernel group_kernel_g(bool sun, bool keep)
 {
-    const size_t lds = group_lds_bytes(G, a.p.R, a.p.J);
-    if (sun && keep)
-        hipLaunchKernelGGL((k_footprint_batch<G, true, true>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
-    else if (sun)
-        hipLaunchKernelGGL((k_footprint_batch<G, true, false>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
-    else if (keep)
-        hipLaunchKernelGGL((k_footprint_batch<G, false, true>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
-    else
-        hipLaunchKernelGGL((k_footprint_batch<G, false, false>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
-    return hipGetLastError();
+    return sun ? (keep ? k_footprint_batch<G, true, true> : k_footprint_batch<G, true, false>)
+               : (keep ? k_footprint_batch<G, false, true> : k_footprint_batch<G, false, false>);
+}
+
+static BatchKernel group_kernel(int G, bool sun, bool keep)
+{
+    return G == 1 ? group_kernel_g<1>(sun, keep) : G == 2 ? group_kernel_g<2>(sun, keep)
+         : G == 4 ? group_kernel_g<4>(sun, keep) : nullptr;
+}
+
+template <int NP>
+static BatchKernel wave_kernel_p(bool sun, bool keep)
+{
+    return sun ? (keep ? k_footprint_batch_wave<NP, true, true> : k_footprint_batch_wave<NP, true, false>)
+               : (keep ? k_footprint_batch_wave<NP, false, true> : k_footprint_batch_wave<NP, false, false>);
+}
+
+// one output pass (fewer registers, more waves per SIMD) for short waveforms
+static BatchKernel wave_kernel(int R, bool sun, bool keep)
+{
+    return R <= kWavePassBins ? wave_kernel_p<1>(sun, keep) : wave_kernel_p<kWavePasses>(sun, keep);
+}
+
+int footprint_wave_resident(int R, int J, bool sun, bool keep)
+{
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)wave_kernel(R, sun, keep), kFootprintThreads,
+                                                     group_lds_bytes(kWaves, R, J)) != hipSuccess) {
+        (void)hipGetLastError();
+        n = 1;
+    }
+    return n > 0 ? n : 1;
 }
 
 bool footprint_group_fits(int G, int R, int J, size_t lds_max)
@@ -1772,39 +1804,17 @@ hipError_t launch_footprint(hipStream_t s, const FootprintArgs& a)
 
 hipError_t launch_footprint_batch(hipStream_t s, const BatchArgs& a, int grid, bool sun, bool keep)
 {
-    switch (a.G) {
-    case 1: return launch_batch_g<1>(s, a, grid, sun, keep);
-    case 2: return launch_batch_g<2>(s, a, grid, sun, keep);
-    case 4: return launch_batch_g<4>(s, a, grid, sun, keep);
-    default: return hipErrorInvalidValue;
-    }
+    const BatchKernel k = group_kernel(a.G, sun, keep);
+    if (!k) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kFootprintThreads), group_lds_bytes(a.G, a.p.R, a.p.J), s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_footprint_batch_wave(hipStream_t s, const BatchArgs& a, int grid, bool sun, bool keep)
 {
     if (a.G != kWaves || a.p.R > kWaveMaxBins || !a.tickets) return hipErrorInvalidValue;
-    const size_t lds = group_lds_bytes(kWaves, a.p.R, a.p.J);
-    const dim3 b(kFootprintThreads);
-    // one output pass (fewer registers, more waves per SIMD) for short waveforms
-    if (a.p.R <= kWavePassBins) {
-        if (sun && keep)
-            hipLaunchKernelGGL((k_footprint_batch_wave<1, true, true>), dim3(grid), b, lds, s, a);
-        else if (sun)
-            hipLaunchKernelGGL((k_footprint_batch_wave<1, true, false>), dim3(grid), b, lds, s, a);
-        else if (keep)
-            hipLaunchKernelGGL((k_footprint_batch_wave<1, false, true>), dim3(grid), b, lds, s, a);
-        else
-            hipLaunchKernelGGL((k_footprint_batch_wave<1, false, false>), dim3(grid), b, lds, s, a);
-    } else {
-        if (sun && keep)
-            hipLaunchKernelGGL((k_footprint_batch_wave<kWavePasses, true, true>), dim3(grid), b, lds, s, a);
-        else if (sun)
-            hipLaunchKernelGGL((k_footprint_batch_wave<kWavePasses, true, false>), dim3(grid), b, lds, s, a);
-        else if (keep)
-            hipLaunchKernelGGL((k_footprint_batch_wave<kWavePasses, false, true>), dim3(grid), b, lds, s, a);
-        else
-            hipLaunchKernelGGL((k_footprint_batch_wave<kWavePasses, false, false>), dim3(grid), b, lds, s, a);
-    }
+    hipLaunchKernelGGL(wave_kernel(a.p.R, sun, keep), dim3(grid), dim3(kFootprintThreads),
+                       group_lds_bytes(kWaves, a.p.R, a.p.J), s, a);
     return hipGetLastError();
 }
 

@@ -36,6 +36,8 @@ struct EventPair {
     hipEvent_t a, b;
 };
 
+constexpr int kFallbackCount = kQueueStride + kQueueInts;   // see lidar_sim::s_cnt
+
 // Host copy of a pattern and its beams.
 struct PatternHost {
     uint32_t kind = 0;
@@ -132,7 +134,7 @@ struct lidar_sim {
     DevBuf<int> b_tstats;              // [pre-pass tiles][4] the tiles' statistics
     DevBuf<int32_t> b_prep_off;        // [n_frames + 1] first pre-pass tile of each frame
     int b_prep_tiles = 0;
-    int b_grid = 0;
+    int b_grid = 0, b_grid_wave = 0;   // workgroups of the group and the wave schedule's launch
     bool b_autotuned = false;
     double b_autotune_ms = 0.0;
     hipStream_t capture_stream = nullptr;
@@ -149,7 +151,9 @@ struct lidar_sim {
     DevBuf<SurAux> s_aux;
     DevBuf<int32_t> s_groups_fb;
     DevBuf<int2> s_items;
-    DevBuf<int> s_cnt;                 // [0] fallback items, [1] queue, [2] fallback beams (running)
+    // [0] fallback items, from kQueueStride on the queue's counters, at
+    // kFallbackCount the fallback beams (running)
+    DevBuf<int> s_cnt;
     DevBuf<FrameDev> s_frame;
     FrameDev s_frame_host{};
     uint64_t s_aux_gen = ~0ull;        // pattern generation whose gate decisions s_aux holds
@@ -1075,7 +1079,7 @@ lidar_status enqueue_batch(lidar_sim* h, hipStream_t s, const int2* items, uint6
         ba.tickets = tickets + n_group;
         ba.n_tickets = n_tickets - n_group;
         ba.next_item = h->b_queue.p + kQueueInts;
-        HIP_TRY(h, launch_footprint_batch_wave(s, ba, h->b_grid, sun, keep), "batch wave-schedule launch");
+        HIP_TRY(h, launch_footprint_batch_wave(s, ba, h->b_grid_wave, sun, keep), "batch wave-schedule launch");
     }
     return LIDAR_OK;
 }
@@ -1108,8 +1112,8 @@ lidar_status upload_frame_table(lidar_sim* h)
 // head goes one item per ticket, the cheap tail in runs, and the last tickets
 // are small again so that the workers finish together.  The workers are the
 // workgroups of the group schedule or the waves of the wave schedule; a
-// ticket costs at least min_cost where items allow (each ticket is a queue
-// atomic, which matters when the items are tiny).
+// ticket costs at least min_cost (each ticket is a queue atomic, which matters
+// when the items are tiny) where the items suffice for every worker.
 std::vector<int32_t> build_tickets(const uint64_t* cost, size_t n, uint64_t workers, int32_t first,
                                    uint64_t min_cost = 0)
 {
@@ -1117,6 +1121,7 @@ std::vector<int32_t> build_tickets(const uint64_t* cost, size_t n, uint64_t work
     std::vector<int32_t> tickets;
     uint64_t remaining = 0;
     for (size_t j = 0; j < n; ++j) remaining += cost[j];
+    min_cost = std::min(min_cost, remaining / workers);
     for (size_t j = 0; j < n;) {
         const uint64_t target = remaining / (4 * workers);
         uint64_t acc = 0;
@@ -1195,7 +1200,8 @@ lidar_status autotune_batch(lidar_sim* h, const std::vector<int2>& items, const 
         for (int mode = 0; mode < n_modes && st == LIDAR_OK; ++mode) {
             std::vector<int32_t> tk(1, 0);
             const std::vector<int32_t> runs =
-                build_tickets(cs.data(), cs.size(), (uint64_t)h->b_grid * (mode ? kWavesPerGroup : 1), 0,
+                build_tickets(cs.data(), cs.size(),
+                              mode ? (uint64_t)h->b_grid_wave * kWavesPerGroup : (uint64_t)h->b_grid, 0,
                               mode ? wave_ticket_cost(h) : 0);
             tk.insert(tk.end(), runs.begin(), runs.end());
             he = d_tickets.ensure(tk.size());
@@ -1365,10 +1371,17 @@ lidar_status setup_batch(lidar_sim* h, const lidar_gbuffer_desc* gbs, const lida
     h->b_items_n = total_groups;
     h->b_samples = samples;
     // persistent grid: as many workgroups as the CUs hold at the LDS-bound
-    // occupancy (extra workgroups would find the queue empty and exit)
+    // occupancy (extra workgroups would find the queue empty and exit); the
+    // wave schedule's: those that are resident, an item per wave at most
     const size_t lds = group_lds_bytes(G, R, h->J) + 2048;   // + static LDS
     const size_t per_cu = std::max<size_t>(1, std::min<size_t>(8, (160 * 1024) / lds));
     h->b_grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)h->cus * per_cu, total_groups));
+    h->b_grid_wave = 1;
+    if (wave_schedule_ok(h)) {
+        const int held = h->cus * footprint_wave_resident((int)R, h->J, h->prm.sun_irradiance != 0.0,
+                                                          (h->prm.flags & LIDAR_KEEP_WAVEFORMS) != 0);
+        h->b_grid_wave = (int)std::min<uint64_t>((uint64_t)held, (total_groups + kWavesPerGroup - 1) / kWavesPerGroup);
+    }
     // schedule per frame: remembered from an earlier autotuning of the class,
     // else the wave schedule where most groups hold a single beam (three of
     // the four waves of a group would idle), then the autotuner if asked
@@ -1425,7 +1438,7 @@ lidar_status setup_batch(lidar_sim* h, const lidar_gbuffer_desc* gbs, const lida
     const std::vector<int32_t> tg = build_tickets(sorted_cost.data(), n_group_items, h->b_grid, 0);
     const std::vector<int32_t> tw =
         build_tickets(sorted_cost.data() + n_group_items, total_groups - n_group_items,
-                      (uint64_t)h->b_grid * kWavesPerGroup, (int32_t)n_group_items, wave_ticket_cost(h));
+                      (uint64_t)h->b_grid_wave * kWavesPerGroup, (int32_t)n_group_items, wave_ticket_cost(h));
     tickets.insert(tickets.end(), tg.begin(), tg.end());
     tickets.insert(tickets.end(), tw.begin(), tw.end());
     h->b_tickets_n = (int)tickets.size() - 1;
@@ -2081,8 +2094,8 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     HIP_TRY(h, h->s_groups_fb.ensure((size_t)fs.n_groups * h->G), "allocate fallback groups");
     HIP_TRY(h, h->s_items.ensure(fs.n_groups), "allocate fallback items");
     if (!h->s_cnt.p) {
-        HIP_TRY(h, h->s_cnt.ensure(4), "allocate counters");
-        HIP_TRY(h, launch_reset_queue(s, h->s_cnt.p, 4), "counter reset");
+        HIP_TRY(h, h->s_cnt.ensure(kFallbackCount + 1), "allocate counters");
+        HIP_TRY(h, launch_reset_queue(s, h->s_cnt.p, kFallbackCount + 1), "counter reset");
     }
     HIP_TRY(h, h->s_frame.ensure(1), "allocate frame table");
     EventPair ev{};
@@ -2094,7 +2107,7 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     }
     LIDAR_TRY(sur_inputs(h, fs, h->s_X.p));
     HIP_TRY(h, sur_infer(s, h->net, h->s_X.p, B, h->work.Y.p), "surrogate forward");
-    HIP_TRY(h, launch_reset_queue(s, h->s_cnt.p, 2), "counter reset");
+    HIP_TRY(h, launch_reset_queue(s, h->s_cnt.p, kFallbackCount), "counter reset");
     DecodeArgs da;
     da.Y = h->work.Y.p;
     da.aux = h->s_aux.p;
@@ -2118,7 +2131,7 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     cp.groups_fb = h->s_groups_fb.p;
     cp.items = h->s_items.p;
     cp.n_items = h->s_cnt.p;
-    cp.n_fallback = h->s_cnt.p + 2;
+    cp.n_fallback = h->s_cnt.p + kFallbackCount;
     HIP_TRY(h, launch_compact(s, cp), "fallback selection launch");
     // the plain path over the selected groups (count read on the device)
     const FrameDev fd = frame_view(h, fs, h->d_beams.p, h->d_echoes.p, h->d_counts.p,
@@ -2136,7 +2149,7 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     ba.items = h->s_items.p;
     ba.n_items = fs.n_groups;
     ba.G = h->G;
-    ba.next_item = h->s_cnt.p + 1;
+    ba.next_item = h->s_cnt.p + kQueueStride;
     ba.n_items_dev = h->s_cnt.p;
     ba.tickets = nullptr;
     ba.n_tickets = 0;
@@ -2238,7 +2251,7 @@ lidar_status lidar_sim_batch_info(lidar_sim* h, lidar_batch_info* out)
     bi.n_beams = h->beam_off.back();
     bi.n_items = h->b_items_n;
     bi.samples = h->b_samples;
-    bi.grid = (uint32_t)h->b_grid;
+    bi.grid = (uint32_t)(h->b_tickets_g > 0 ? h->b_grid : h->b_grid_wave);
     bi.graph = h->graph_exec ? 1u : 0u;
     bi.autotuned = h->b_autotuned ? 1u : 0u;
     bi.wave_items = (uint32_t)h->b_wave_items;
@@ -2482,7 +2495,7 @@ lidar_status lidar_sim_get_stats(lidar_sim* h, lidar_stats* out)
     h->st.kernel_h = h->setup_ok ? (uint32_t)h->single.k.KH : 0;
     if (h->s_cnt.p) {
         int fb = 0;
-        HIP_TRY(h, hipMemcpyAsync(&fb, h->s_cnt.p + 2, sizeof(int), hipMemcpyDeviceToHost, h->stream),
+        HIP_TRY(h, hipMemcpyAsync(&fb, h->s_cnt.p + kFallbackCount, sizeof(int), hipMemcpyDeviceToHost, h->stream),
                 "copy fallback count");
         HIP_TRY(h, hipStreamSynchronize(h->stream), "stats synchronise");
         h->st.fallback_beams = (uint64_t)fb;
@@ -2506,7 +2519,7 @@ lidar_status lidar_sim_reset_stats(lidar_sim* h)
     h->st.fallback_beams = 0;
     h->st.surrogate_ms = 0.0;
     h->st.surrogate_frames = 0;
-    if (h->s_cnt.p) HIP_TRY(h, launch_reset_queue(h->stream, h->s_cnt.p + 2, 1), "counter reset");
+    if (h->s_cnt.p) HIP_TRY(h, launch_reset_queue(h->stream, h->s_cnt.p + kFallbackCount, 1), "counter reset");
     return LIDAR_OK;
 }
 
