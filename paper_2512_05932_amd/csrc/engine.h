@@ -565,8 +565,8 @@ hipError_t launch_aux_out(hipStream_t s, const SurAux* aux, int B, float* out);
 // NaN rows of the kept waveforms [B][R] of accepted beams
 hipError_t launch_fill_accepted(hipStream_t s, const SurAux* aux, int B, int R, float* waves);
 
-// fused inference: X [n][1056] BF16 -> Y [n][16] FP32, transposed BF16
-// weights Wt1 [256][1056], Wt2, Wt3 [256][256], Wt4 [16][256]
+// fused inference: X [n][1056] BF16 -> Y [n][16] FP32, BF16 weights in the
+// kernel's fragment order (launch_transpose_weights), layer after layer
 struct InferArgs {
     const uint16_t* X;
     long n;
@@ -581,7 +581,7 @@ hipError_t launch_mlp_infer(hipStream_t s, const InferArgs& a);
 struct SurNet {
     DevBuf<float> theta, m, v, grad;    // FP32 [kSurParams]
     DevBuf<uint16_t> theta_b;           // BF16 operand copy
-    DevBuf<uint16_t> theta_t;           // transposed BF16 weights [kSurWtSize]
+    DevBuf<uint16_t> theta_t;           // BF16 weights in fragment order [kSurWtSize]
     bool t_stale = true;
     long step = 0;
     bool ready = false;

@@ -17,7 +17,6 @@ namespace {
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16v4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTileM = 64, kTileN = 64, kTileK = 32;
 constexpr int kLdsK = kTileK + 8;         // row stride in LDS (elements)
@@ -410,177 +409,184 @@ __global__ void k_to_bf16(const float* x, uint16_t* y, long n)
     if (i < n) y[i] = to_bf16(x[i]);
 }
 
-// BF16 operand copies transposed to [out][in] (inputs contiguous) for the
-// fused inference kernel.
-__global__ void k_transpose_bf16(const uint16_t* W, int in, int out, uint16_t* Wt)
+// Place of feature f inside its block of 32 inputs of a hidden layer: the
+// fused inference kernel's MFMA fragments hold features 4 q .. 4 q + 3 and 16 +
+// 4 q .. 16 + 4 q + 3 of a block at the eight K positions of lane quad q.
+__device__ inline int frag_place(int f) { return 8 * ((f & 15) >> 2) + ((f & 16) >> 2) + (f & 3); }
+
+// BF16 operand copies for the fused inference kernel in the order of its
+// fragments: blocks of 32 inputs x 16 outputs, lane by lane (output l % 16, the
+// eight K positions of quad l / 16; hidden layers' inputs at frag_place), so
+// that a wave reads a fragment as one contiguous kilobyte.
+__global__ void k_weight_fragments(const uint16_t* W, int in, int out, bool hidden, uint16_t* Wt)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long)in * out) return;
-    const int k = (int)(i / out), n = (int)(i % out);
-    Wt[(long)n * in + k] = W[i];
+    const int k = (int)(i / out), n = (int)(i % out), p = hidden ? frag_place(k & 31) : k & 31;
+    Wt[(((long)(k >> 5) * (out / 16) + n / 16) * 64 + (p >> 3) * 16 + n % 16) * 8 + (p & 7)] = W[i];
 }
 
-// Fused inference with the activations in registers.  The weights are the
-// MFMA's A operand (a tile of 16 output features) and the beams its B operand
-// (16 rows), so a wave holds all 256 features of its 16 beams.  The output of
-// v_mfma_f32_16x16x32_bf16 (lane l: features 4 (l / 16) .. + 3 of row l % 16)
-// is the next layer's B operand as it stands once both operands of a K step
-// of 32 take the features in the same order: lane quad q and element e stand
-// for feature 32 s + 4 q + e (e < 4) or 32 s + 16 + 4 q + (e - 4).  The first
-// layer reads its inputs in natural order (8 q + e).  Weight tiles (256 x 32)
-// are staged in double-buffered LDS, shared by the workgroup's 8 waves (128
-// beams); the tiles of step k + 2 are loaded while step k's MFMAs run.
-constexpr int kInfWaves = 8;
-constexpr int kInfRows = 16 * kInfWaves;     // rows (beams) per workgroup
+// Fused inference: a workgroup of four waves takes kInfRows rows (beams) through
+// all four layers.  The weights are the MFMA's A operand (tiles of 16 output
+// features), the rows its B operand; a wave holds 64 features of the 64 rows
+// (4 x 4 tiles), so that a K step of 32 needs four fragments of each for 16
+// MFMAs.  No two waves share a feature: weight fragments go from memory (L2,
+// 0.8 MB) straight into registers, two K steps ahead.  The first layer's rows,
+// which all waves need, are staged in double-buffered LDS, 64 columns a stage,
+// loaded three stages ahead because they come from HBM; the activations
+// between layers lie over them, so that three workgroups fit a CU (168 VGPRs) and one's
+// GELUs (about as long as its MFMAs) run beside another's products.  The output
+// of v_mfma_f32_16x16x32_bf16 (lane l: features 4 (l / 16) .. + 3 of row l % 16)
+// is stored in the order of the next layer's fragments (frag_place; its
+// weights lie in the same order), 16 bytes for two tiles.  Sums run over the K
+// steps in ascending order.
+// 128000 rows: 217 us with 16 rows and all 256 features per wave (every MFMA read
+// its weight fragment from LDS), 167 us with this tile and the weights staged in
+// LDS, 137 us with them straight from memory (141 us at two workgroups per CU), and
+// 132 us with the MFMAs at raised wave priority: 104 GFLOP, 790 TFLOP/s.
+constexpr int kInfWaves = 4;
+constexpr int kInfRows = 64;                 // rows (beams) per workgroup
 constexpr int kInfThreads = 64 * kInfWaves;
-constexpr int kInfK = 32;                    // K step
-constexpr int kInfLdsK = kInfK + 8;          // staged row stride (elements)
-constexpr int kInfAhead = 2;                 // K steps loaded ahead of their use
+constexpr int kInfXK = 64;                   // row columns of a stage
+constexpr int kInfLdX = kInfXK + 8;          // LDS row strides (elements): 16-byte reads
+constexpr int kInfLdH = kSurHid + 8;         // of 8 rows touch all banks once
 
-struct InferLds {
-    uint16_t Bs[2][kSurHid][kInfLdsK];       // weight tiles [out][k]
+union InferLds {
+    uint16_t X[2][kInfRows][kInfLdX];        // row stages of the first layer
+    uint16_t H[kInfRows][kInfLdH];           // activations [row][feature, fragment order]
 };
 
 __device__ inline bf16x8 ld8(const uint16_t* p) { return *(const bf16x8*)p; }
 
-// the workgroup's share of one weight tile: 1024 chunks of 8 elements,
-// kStage per thread (chunk c: row c / 4, elements 8 (c % 4) .. + 7)
-constexpr int kStage = 4 * kSurHid / kInfThreads;
-__device__ inline void stage_load(const uint16_t* Wt, int K, int k0, int tid, bf16x8 (&r)[kStage])
+constexpr int kInfS1 = kSurIn / 32;          // K steps of the first layer
+constexpr int kInfSH = kSurHid / 32;         // of a hidden one
+constexpr int kInfSteps = kInfS1 + 2 * kInfSH;
+constexpr int kInfX = (kSurIn + kInfXK - 1) / kInfXK;        // row stages, the last one half
+constexpr int kInfPieces = kInfRows * kInfXK / 8 / kInfThreads;   // 16-byte pieces of a stage per thread
+static_assert(kSurIn % 32 == 0 && kInfSH % 2 == 0 && kInfRows == 64, "whole K steps");
+
+// bias + GELU of the wave's 64 x 64 block into the activations
+__device__ inline void store_hidden(InferLds& L, const f32x4 (&acc)[4][4], const float* bias, int wave, int l16, int q)
 {
 #pragma unroll
-    for (int c = 0; c < kStage; ++c) {
-        const int q = tid + kInfThreads * c;
-        r[c] = ld8(Wt + (long)(q >> 2) * K + k0 + 8 * (q & 3));
-    }
-}
-
-__device__ inline void stage_store(InferLds& L, int buf, int tid, const bf16x8 (&r)[kStage])
-{
+    for (int p = 0; p < 2; ++p) {
+        const int f = 64 * wave + 32 * p;
+        const float4 b0 = *(const float4*)(bias + f + 4 * q), b1 = *(const float4*)(bias + f + 16 + 4 * q);
 #pragma unroll
-    for (int c = 0; c < kStage; ++c) {
-        const int q = tid + kInfThreads * c;
-        *(bf16x8*)&L.Bs[buf][q >> 2][8 * (q & 3)] = r[c];
-    }
-}
-
-// A fragment of tile t in the permuted order (hidden layers)
-__device__ inline bf16x8 frag_perm(const InferLds& L, int buf, int t, int l16, int q)
-{
-    const bf16v4 lo = *(const bf16v4*)&L.Bs[buf][16 * t + l16][4 * q];
-    const bf16v4 hi = *(const bf16v4*)&L.Bs[buf][16 * t + l16][16 + 4 * q];
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-__device__ inline __bf16 bf(float x) { return __builtin_bit_cast(__bf16, to_bf16(x)); }
-
-// bias + GELU of the wave's 16 x 256 block into B fragments of the next layer
-__device__ inline void to_frags(const f32x4 (&acc)[16], const float* bias, int q, bf16x8 (&h)[8])
-{
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const float4 b0 = *(const float4*)(bias + 32 * s + 4 * q);
-        const float4 b1 = *(const float4*)(bias + 32 * s + 16 + 4 * q);
-        const f32x4 x0 = acc[2 * s], x1 = acc[2 * s + 1];
-        h[s] = bf16x8{bf(gelu(x0[0] + b0.x)), bf(gelu(x0[1] + b0.y)), bf(gelu(x0[2] + b0.z)),
-                      bf(gelu(x0[3] + b0.w)), bf(gelu(x1[0] + b1.x)), bf(gelu(x1[1] + b1.y)),
-                      bf(gelu(x1[2] + b1.z)), bf(gelu(x1[3] + b1.w))};
-    }
-}
-
-// First layer: acc = W1 x over the 1056 inputs (B fragments straight from X).
-__device__ inline void layer_first(const uint16_t* X, long row, long n, InferLds& L,
-                                   const uint16_t* Wt, f32x4 (&acc)[16])
-{
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    constexpr int S = kSurIn / kInfK;
-#pragma unroll
-    for (int t = 0; t < 16; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8 rb[kInfAhead][kStage], xb[kInfAhead];
-    auto xload = [&](int st) { return row < n ? ld8(X + row * kSurIn + st * kInfK + 8 * q) : bf16x8{}; };
-#pragma unroll
-    for (int u = 0; u < kInfAhead; ++u) {
-        stage_load(Wt, kSurIn, u * kInfK, tid, rb[u]);
-        xb[u] = xload(u);
-    }
-    stage_store(L, 0, tid, rb[0]);
-    __syncthreads();
-    for (int st0 = 0; st0 < S; st0 += kInfAhead) {
-#pragma unroll
-        for (int u = 0; u < kInfAhead; ++u) {
-            const int st = st0 + u;                      // ring slot u
-            if (st >= S) break;
-            const int buf = st & 1;
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                const bf16x8 a = *(const bf16x8*)&L.Bs[buf][16 * t + l16][8 * q];
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, xb[u], acc[t], 0, 0, 0);
-            }
-            const int un = (u + 1) % kInfAhead;
-            if (st + 1 < S) stage_store(L, buf ^ 1, tid, rb[un]);
-            if (st + kInfAhead < S) {
-                stage_load(Wt, kSurIn, (st + kInfAhead) * kInfK, tid, rb[u]);
-                xb[u] = xload(st + kInfAhead);
-            }
-            __syncthreads();
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 x = acc[2 * p][j], y = acc[2 * p + 1][j];
+            const bf16x8 h = {(__bf16)gelu(x[0] + b0.x), (__bf16)gelu(x[1] + b0.y), (__bf16)gelu(x[2] + b0.z),
+                              (__bf16)gelu(x[3] + b0.w), (__bf16)gelu(y[0] + b1.x), (__bf16)gelu(y[1] + b1.y),
+                              (__bf16)gelu(y[2] + b1.z), (__bf16)gelu(y[3] + b1.w)};
+            *(bf16x8*)&L.H[16 * j + l16][f + 8 * q] = h;
         }
     }
 }
 
-// Hidden layer: acc = W h over 256 inputs held as B fragments.
-__device__ inline void layer_hidden(const bf16x8 (&h)[8], InferLds& L, const uint16_t* Wt,
-                                    f32x4 (&acc)[16])
-{
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    constexpr int S = kSurHid / kInfK;
-#pragma unroll
-    for (int t = 0; t < 16; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8 rb[kInfAhead][kStage];
-#pragma unroll
-    for (int u = 0; u < kInfAhead; ++u) stage_load(Wt, kSurHid, u * kInfK, tid, rb[u]);
-    stage_store(L, 0, tid, rb[0]);
-    __syncthreads();
-#pragma unroll
-    for (int st = 0; st < S; ++st) {
-        const int buf = st & 1, u = st % kInfAhead;
-#pragma unroll
-        for (int t = 0; t < 16; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_perm(L, buf, t, l16, q), h[st],
-                                                             acc[t], 0, 0, 0);
-        if (st + 1 < S) stage_store(L, buf ^ 1, tid, rb[(u + 1) % kInfAhead]);
-        if (st + kInfAhead < S) stage_load(Wt, kSurHid, (st + kInfAhead) * kInfK, tid, rb[u]);
-        __syncthreads();
-    }
-}
-
-// The whole network for 128 rows per workgroup, 16 per wave.
-__global__ __launch_bounds__(kInfThreads) void k_mlp_infer(InferArgs a)
+__global__ __launch_bounds__(kInfThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_infer(InferArgs a)
 {
     extern __shared__ float4 lds_v4[];
     InferLds& L = *(InferLds*)lds_v4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q = lane >> 4;
-    const long row = (long)blockIdx.x * kInfRows + 16 * wave + l16;
-    f32x4 acc[16];
-    bf16x8 h[8];
-    layer_first(a.X, row, a.n, L, a.Wt1, acc);
-    to_frags(acc, a.b1, q, h);
-    layer_hidden(h, L, a.Wt2, acc);
-    to_frags(acc, a.b2, q, h);
-    layer_hidden(h, L, a.Wt3, acc);
-    to_frags(acc, a.b3, q, h);
-    // output layer: one tile of 16 outputs, weights read directly (8 KB)
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long row0 = (long)blockIdx.x * kInfRows;
+    // weight fragments of K step g (the layers' steps follow each other in
+    // memory), two steps in turn
+    const uint16_t* wsrc = a.Wt1 + (4 * wave * 64 + lane) * 8;
+    bf16x8 w[2][4];
+    auto wload = [&](int g, bf16x8 (&f)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = ld8(wsrc + ((long)g * (kSurHid / 16) + i) * 512);
+    };
+    // rows of the first layer: pieces tid and tid + kInfThreads of a stage (rows
+    // past n repeat the last one; their outputs are not stored)
+    const uint16_t* xsrc[kInfPieces];
+    bf16x8 x[2][kInfPieces];
+#pragma unroll
+    for (int i = 0; i < kInfPieces; ++i)
+        xsrc[i] = a.X + min(row0 + (tid >> 3) + kInfThreads / 8 * i, a.n - 1) * kSurIn + 8 * (tid & 7);
+    auto xload = [&](int s, bf16x8 (&r)[kInfPieces]) {
+        if (kInfXK * s + 8 * (tid & 7) < kSurIn)
+#pragma unroll
+            for (int i = 0; i < kInfPieces; ++i) r[i] = ld8(xsrc[i] + kInfXK * s);
+    };
+    auto xstore = [&](int s, const bf16x8 (&r)[kInfPieces]) {
+#pragma unroll
+        for (int i = 0; i < kInfPieces; ++i)
+            *(bf16x8*)&L.X[s & 1][(tid >> 3) + kInfThreads / 8 * i][8 * (tid & 7)] = r[i];
+    };
+    f32x4 acc[4][4];                                // [feature tile][row tile]
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    // K step g: its fragments meet the rows' in b, then take step g + 2
+    auto step = [&](int g, bf16x8 (&f)[4], const bf16x8 (&b)[4]) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i], b[j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        if (g + 2 < kInfSteps) wload(g + 2, f);
+    };
+    xload(0, x[0]);
+    wload(0, w[0]);
+    wload(1, w[1]);
+    xload(1, x[1]);
+    xstore(0, x[0]);
+    xload(2, x[0]);
+    __syncthreads();
+    clear();
+    // row stage s: the next one goes to LDS (its buffer was read in stage s - 1),
+    // and its registers take a later one
+    for (int s0 = 0; s0 < kInfX; s0 += 2) {
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int s = s0 + v;
+            if (s >= kInfX) break;
+            if (s + 1 < kInfX) xstore(s + 1, x[(v + 1) & 1]);
+            if (s + 3 < kInfX) xload(s + 3, x[(v + 1) & 1]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (2 * s + u >= kInfS1) break;
+                bf16x8 b[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) b[j] = ld8(&L.X[v][16 * j + l16][32 * u + 8 * q]);
+                step(2 * s + u, w[u], b);
+            }
+            __syncthreads();
+        }
+    }
+    store_hidden(L, acc, a.b1, wave, l16, q);
+    __syncthreads();
+#pragma unroll 1
+    for (int l = 0; l < 2; ++l) {
+        clear();
+#pragma unroll
+        for (int t = 0; t < kInfSH; ++t) {
+            bf16x8 b[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[j] = ld8(&L.H[16 * j + l16][32 * t + 8 * q]);
+            step(kInfS1 + kInfSH * l + t, w[(kInfS1 + t) & 1], b);
+        }
+        __syncthreads();                                 // every read of H is done
+        store_hidden(L, acc, l == 0 ? a.b2 : a.b3, wave, l16, q);
+        __syncthreads();
+    }
+    // output layer: one tile of 16 outputs for 16 rows per wave
+    const int r = 16 * wave + l16;
     f32x4 y = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const uint16_t* w = a.Wt4 + (long)l16 * kSurHid + 32 * s;
-        const bf16v4 lo = *(const bf16v4*)(w + 4 * q), hi = *(const bf16v4*)(w + 16 + 4 * q);
-        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7),
-                                                    h[s], y, 0, 0, 0);
-    }
-    if (row < a.n) {
+    for (int t = 0; t < kInfSH; ++t)
+        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(a.Wt4 + (t * 64 + lane) * 8), ld8(&L.H[r][32 * t + 8 * q]), y,
+                                                    0, 0, 0);
+    if (row0 + r < a.n) {
         const float4 b4 = *(const float4*)(a.b4 + 4 * q);
-        *(float4*)(a.Y + row * kSurOut + 4 * q) = make_float4(y[0] + b4.x, y[1] + b4.y, y[2] + b4.z,
-                                                              y[3] + b4.w);
+        *(float4*)(a.Y + (row0 + r) * kSurOut + 4 * q) = make_float4(y[0] + b4.x, y[1] + b4.y, y[2] + b4.z, y[3] + b4.w);
     }
 }
 
@@ -597,8 +603,8 @@ hipError_t launch_transpose_weights(hipStream_t s, const uint16_t* theta_b, uint
                      {kSurOffW4, (long)kSurIn * kSurHid + 2L * kSurHid * kSurHid, kSurHid, kSurOut}};
     for (const L& l : ls) {
         const long n = (long)l.in * l.out;
-        hipLaunchKernelGGL(k_transpose_bf16, dim3(blocks(n, 256)), dim3(256), 0, s, theta_b + l.off,
-                           l.in, l.out, wt + l.toff);
+        hipLaunchKernelGGL(k_weight_fragments, dim3(blocks(n, 256)), dim3(256), 0, s, theta_b + l.off,
+                           l.in, l.out, l.off != kSurOffW1, wt + l.toff);
     }
     return hipGetLastError();
 }
