@@ -258,6 +258,8 @@ struct FootprintArgs {
     int n_groups, G, chunk;     // chunk = ceil(n_groups / kXcds)
 };
 hipError_t launch_footprint(hipStream_t s, const FootprintArgs& a);
+// the same with a wave per group (a.G == 4, R <= kWaveMaxBins)
+hipError_t launch_footprint_wave(hipStream_t s, const FootprintArgs& a);
 
 // Persistent launch over the (frame, group) items of a batch.
 struct BatchArgs {

@@ -1336,7 +1336,7 @@ __device__ inline void clear_passes(float* hist, int R, unsigned dirty, unsigned
 // floor throughout, holds no run, and only its edge bins can be read, as the
 // crossings of runs in the neighbouring passes).
 
-template <int NP, bool SUN, bool KEEP>
+template <int NP, bool SUN, bool KEEP, bool FX = (NP > 1)>
 __device__ __attribute__((always_inline)) inline int process_beam_wave(
     const FrameDev& f, const PathDev& p, int beam, float* hist, int RS, const float* taps, unsigned* nzw,
     unsigned* am, int lane, unsigned long long* rk, int2* rb)
@@ -1356,7 +1356,7 @@ __device__ __attribute__((always_inline)) inline int process_beam_wave(
     // in the instance for waveforms of up to 512 bins, whose registers are
     // budgeted for eight waves per SIMD)
     IntAcc ia{0.0f, 0, false};
-    const int span = NP > 1 && win ? fixed_unit(f, (float)bi.samples, R, &ia) : 0;
+    const int span = FX && win ? fixed_unit(f, (float)bi.samples, R, &ia) : 0;
     auto gather = [&](auto iacc, auto each, float* acc) {
         constexpr bool I = decltype(iacc)::value, E = decltype(each)::value;
         if (f.tile == 64)
@@ -1374,7 +1374,7 @@ __device__ __attribute__((always_inline)) inline int process_beam_wave(
         gather_direct<SUN>(f, R, u, v, r0, r1, q0, q1, hist, nzw, nzs, lane, &sacc);
     else if (win) {
         bool done = false;
-        if constexpr (NP > 1) {
+        if constexpr (FX) {
             if (span) {
                 if (ia.each) gather(std::true_type{}, std::true_type{}, &sacc);
                 else gather(std::true_type{}, std::false_type{}, &sacc);
@@ -1388,7 +1388,7 @@ __device__ __attribute__((always_inline)) inline int process_beam_wave(
     if (f.floor_given) floor_b = bi.floor;
     wave_sync();                                         // the histogram is complete
     int fx = 0;                                          // 1: fixed point, 3: fixed point run again
-    if (NP > 1 && span) {
+    if (FX && span) {
         // integers to FP32 bins in place; a beam whose truncation bound is
         // too coarse runs again with FP32 atomics
         const float vmax = fixed_to_float(hist, span, ia, lane);
@@ -1725,6 +1725,53 @@ void k_footprint_batch_wave(BatchArgs a)
     }
 }
 
+// The single-frame kernel in the wave schedule: the waves take a group each,
+// then the ones after, and run their beams one by one in a histogram slot of
+// their own (FP32 LDS atomics; NP and the steps as in the batch's wave
+// schedule).  Narrow beams are bound by latency, a chain of dependent loads,
+// the pulse and the search for echoes: four waves per beam meet at a barrier
+// for each of these steps and three of them idle in most.  Frames with
+// 2048 bins, times with the pre-pass (about 20 us): 8000 beams of 100 samples
+// 76 us in groups, 49 us here; 32000 beams 225 us and 104 us.
+template <int NP, bool SUN, bool KEEP>
+__global__ __launch_bounds__(kFootprintThreads) __attribute__((amdgpu_waves_per_eu(NP == 1 ? 8 : 4)))
+void k_footprint_wave(FootprintArgs a)
+{
+    constexpr int G = kWaves;
+    extern __shared__ float4 lds4[];
+    const int RS = conv_stride(a.p.R, a.p.J);
+    float* taps = (float*)lds4 + G * RS;
+    __shared__ unsigned nzw[kWaves];
+    __shared__ unsigned amask[kWaves][kMaxBins / kPassBins + 1];
+    __shared__ unsigned long long rkey[kWaves][kMaxEchoes];   // first runs: peak keys, bins
+    __shared__ int2 rbin[kWaves][kMaxEchoes];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    load_taps(taps, a.p.taps, a.p.J, tid);
+    clear_group(lds4, G * RS / 4, &nzw[0], tid);
+    __syncthreads();
+    float* hist = (float*)(lds4 + wave * (RS / 4)) + conv_pad(a.p.J);
+    int left = 0;                                        // what the last beam left in the slot
+    // a.chunk consecutive groups per XCD, dealt round its waves
+    const int g0 = blockIdx.x % kXcds * a.chunk, g1 = min(a.n_groups, g0 + a.chunk);
+    const int step = gridDim.x / kXcds * kWaves;         // uniform over the wave; no barrier follows
+    for (int gi = g0 + blockIdx.x / kXcds * kWaves + wave; gi < g1; gi += step) {
+        int4 mem = load_uniform((const int4*)a.groups + gi);
+#pragma unroll 1
+        for (int m = 0; m < G; ++m) {
+            const int beam = mem.x;
+            mem = make_int4(mem.y, mem.z, mem.w, -1);
+            if (beam < 0) break;                         // members come first
+            clear_passes<NP>(hist, a.p.R, (unsigned)left >> 8 & 0xffu, (unsigned)left >> 16 & 0xffu, lane);
+            if (lane == 0) nzw[wave] = 0u;
+            wave_sync();
+            left = process_beam_wave<NP, SUN, KEEP, false>(a.f, a.p, beam, hist, RS, taps, &nzw[wave],
+                                                           amask[wave], lane, rkey[wave], rbin[wave]);
+            wave_sync();                                 // the slot is reused
+        }
+    }
+}
+
 __global__ void k_reset_queue(int* counter, int n)
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
@@ -1745,6 +1792,29 @@ static hipError_t launch_g(hipStream_t s, const FootprintArgs& a)
         hipLaunchKernelGGL((k_footprint<G, false, true>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
     else
         hipLaunchKernelGGL((k_footprint<G, false, false>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
+    return hipGetLastError();
+}
+
+constexpr int kWaveGridPerXcd = 8 * 32;
+
+template <int NP>
+static hipError_t launch_wave_p(hipStream_t s, const FootprintArgs& a)
+{
+    // NP > 1: at most eight workgroups per CU, half of them resident at a time
+    // (32000 beams of 105 samples, 2048 bins: 117 us for the frame with a
+    // workgroup per four groups, 104 us with these; with 512 bins 64 and 70)
+    const int per_xcd = (a.chunk + kWaves - 1) / kWaves;
+    const int grid = kXcds * (NP > 1 && per_xcd > kWaveGridPerXcd ? kWaveGridPerXcd : per_xcd);
+    const size_t lds = group_lds_bytes(kWaves, a.p.R, a.p.J);
+    const bool sun = a.f.sun != nullptr && !a.f.floor_given, keep = a.f.waves != nullptr;
+    if (sun && keep)
+        hipLaunchKernelGGL((k_footprint_wave<NP, true, true>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
+    else if (sun)
+        hipLaunchKernelGGL((k_footprint_wave<NP, true, false>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
+    else if (keep)
+        hipLaunchKernelGGL((k_footprint_wave<NP, false, true>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
+    else
+        hipLaunchKernelGGL((k_footprint_wave<NP, false, false>), dim3(grid), dim3(kFootprintThreads), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1800,6 +1870,12 @@ hipError_t launch_footprint(hipStream_t s, const FootprintArgs& a)
     case 4: return launch_g<4>(s, a);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_footprint_wave(hipStream_t s, const FootprintArgs& a)
+{
+    if (a.G != kWaves || a.p.R > kWaveMaxBins) return hipErrorInvalidValue;
+    return a.p.R <= kWavePassBins ? launch_wave_p<1>(s, a) : launch_wave_p<kWavePasses>(s, a);
 }
 
 hipError_t launch_footprint_batch(hipStream_t s, const BatchArgs& a, int grid, bool sun, bool keep)

@@ -853,6 +853,23 @@ FrameDev frame_view(const lidar_sim* h, const FrameState& fs, lidar_beam_info* b
     return f;
 }
 
+// Whether a single frame of B beams runs in the wave schedule: one histogram
+// slot per wave, waveforms short enough for registers, beams enough to fill
+// the chip with a wave each, and kernels so small that a wave's longer gather
+// costs less than a group's barriers.  Where groups hold one beam the bound on
+// the kernel's cells grows with the beams that hide a wave's latency; where
+// they share their pixels' reads it is fixed.  Frames with 512 bins, groups
+// against waves: 1000 beams of 20 samples 14.8 and 14.6 us, 2048 beams 20.8
+// and 19.5, 4000 beams 30.7 and 22.3; single beams of 400 samples: 2048 beams
+// 38 and 46 us, 4000 beams 47 and 40; of 1500 samples: 8000 beams 86 and 67;
+// shared: 8000 beams of 100 samples 51 and 31 us, of 400 samples 50 and 66.
+bool frame_in_waves(const FootprintArgs& a, size_t B)
+{
+    if (a.G != kWavesPerGroup || a.p.R > kWaveMaxBins || B < 2048) return false;
+    const size_t cells = (size_t)a.f.KW * a.f.KH;
+    return cells <= (B < 2 * (size_t)a.n_groups ? std::min<size_t>(B / 6, 2000) : 160);
+}
+
 PathDev path_view(const lidar_sim* h)
 {
     PathDev p;
@@ -1695,7 +1712,7 @@ lidar_status simulate_static(const lidar_sim_params* prm, const lidar_pattern_de
     fa.n_groups = fs.n_groups;
     fa.G = G;
     fa.chunk = (fs.n_groups + kXcds - 1) / kXcds;
-    HIP_TRY(h, launch_footprint(s, fa), "footprint launch");
+    HIP_TRY(h, frame_in_waves(fa, B) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa), "footprint launch");
     return LIDAR_OK;
 }
 
@@ -2048,7 +2065,7 @@ lidar_status lidar_sim_simulate_frame(lidar_sim* h, uint32_t mode)
     if (corr || det)
         HIP_TRY(h, launch_footprint_one(s, fa, corr, det), "footprint launch");
     else
-        HIP_TRY(h, launch_footprint(s, fa), "footprint launch");
+        HIP_TRY(h, frame_in_waves(fa, B) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa), "footprint launch");
     if (prof) {
         HIP_TRY(h, hipEventRecord(fp.b, s), "record event");
         h->pending_pp.push_back(pp);
