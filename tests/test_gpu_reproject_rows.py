@@ -1,0 +1,33 @@
+"""Reprojection onto rasters whose rows and columns do not fill the kernel's blocks (256 columns x 8 rows), against the
+FP64 oracle: depths, reflectance and gain are the same FP32 values, normals agree to FP32 rounding."""
+import numpy as np
+import pytest
+
+import scenes
+from oracle import pinhole as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("width,height", [(1, 1), (255, 7), (256, 8), (257, 9), (300, 17)])
+def test_ragged_rasters(width, height):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2512_05932_amd as lidar
+    src = scenes.pinhole_render(6, width=320, height=180, hfov_deg=70.0, pitch_deg=-3.0, fmt=P.DEPTH_EYE_Z)
+    raster = scenes.Raster(width, height, -30.0, 30.0, -12.0, 2.0)
+    planes = [torch.from_numpy(np.ascontiguousarray(p)).cuda()
+              for p in (src.depth, src.reflectance, src.retro_gain, *src.normal)]
+    params = scenes.iid_frame(0).params
+    sim = lidar.LidarSim(params, stream=torch.cuda.current_stream())
+    try:
+        sim.set_gbuffer_pinhole(src, planes, raster)
+        got = sim.read_gbuffer()
+    finally:
+        sim.close()
+    ref = P.reproject(src.as_dict(), raster)
+    for k in range(3):
+        np.testing.assert_array_equal(got[k], ref[k].astype(np.float32))
+    for k in range(3):
+        np.testing.assert_allclose(got[3 + k], ref[3][k], atol=1e-7)
