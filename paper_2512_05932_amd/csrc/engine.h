@@ -255,7 +255,8 @@ struct FootprintArgs {
     FrameDev f;
     PathDev p;
     const int32_t* groups;      // [n_groups][G] beam indices, -1 = empty slot
-    int n_groups, G, chunk;     // chunk = ceil(n_groups / kXcds)
+    int n_groups, G;
+    int chunk, band;            // groups per XCD, in bands of consecutive ones
 };
 hipError_t launch_footprint(hipStream_t s, const FootprintArgs& a);
 // the same with a wave per group (a.G == 4, R <= kWaveMaxBins)

@@ -1478,6 +1478,14 @@ __device__ inline void load_taps(float* taps, const float* src, int J, int tid)
         taps[j] = (j >= d && j - d <= 2 * J) ? src[j - d] : 0.0f;
 }
 
+// Group of place i in the sequence of XCD x: every XCD takes every kXcds-th
+// band of `band` consecutive groups.
+__device__ inline int group_of(int x, int i, int band)
+{
+    const int q = i / band;
+    return (q * kXcds + x) * band + (i - q * band);
+}
+
 template <int G, bool SUN, bool KEEP>
 __global__ __launch_bounds__(kFootprintThreads)
 void k_footprint(FootprintArgs a)
@@ -1494,8 +1502,7 @@ void k_footprint(FootprintArgs a)
     // s runs on XCD s % 8; each XCD takes one contiguous run of the
     // spatially ordered groups, and the groups in flight on it share their
     // pixels in its L2.
-    const int slot = blockIdx.x;
-    const int gi = (slot % kXcds) * a.chunk + slot / kXcds;
+    const int gi = group_of(blockIdx.x % kXcds, blockIdx.x / kXcds, a.band);
     if (gi >= a.n_groups) return;
     const int tid = threadIdx.x;
     clear_group(lds4, G * RS / 4, &nzmask, tid);
@@ -1520,8 +1527,7 @@ void k_footprint_one(FootprintArgs a)
     __shared__ float red[1][kWaves];
     __shared__ unsigned nzmask;
     __shared__ unsigned amask[1][kMaxBins / kPassBins + 1];
-    const int slot = blockIdx.x;
-    const int gi = (slot % kXcds) * a.chunk + slot / kXcds;
+    const int gi = group_of(blockIdx.x % kXcds, blockIdx.x / kXcds, a.band);
     if (gi >= a.n_groups) return;
     const int tid = threadIdx.x;
     clear_group(lds4, S * RS / 4, &nzmask, tid);
@@ -1752,10 +1758,11 @@ void k_footprint_wave(FootprintArgs a)
     __syncthreads();
     float* hist = (float*)(lds4 + wave * (RS / 4)) + conv_pad(a.p.J);
     int left = 0;                                        // what the last beam left in the slot
-    // a.chunk consecutive groups per XCD, dealt round its waves
-    const int g0 = blockIdx.x % kXcds * a.chunk, g1 = min(a.n_groups, g0 + a.chunk);
+    // the XCD's groups, dealt round its waves
     const int step = gridDim.x / kXcds * kWaves;         // uniform over the wave; no barrier follows
-    for (int gi = g0 + blockIdx.x / kXcds * kWaves + wave; gi < g1; gi += step) {
+    for (int i = blockIdx.x / kXcds * kWaves + wave; i < a.chunk; i += step) {
+        const int gi = group_of(blockIdx.x % kXcds, i, a.band);
+        if (gi >= a.n_groups) continue;
         int4 mem = load_uniform((const int4*)a.groups + gi);
 #pragma unroll 1
         for (int m = 0; m < G; ++m) {
