@@ -498,9 +498,10 @@ struct CoarseArgs {
     int R;
     float sun_x, sun_y, sun_z;
     SurGeom g;
-    float4* cell;               // [CH][CW] {mean depth, reflectance cover, mean gain, mean cos}
+    // [CH][CW] {mean depth, sum of shade, BF16 pair {reflectance cover, log10 of
+    // the mean gain / 3}, BF16 mean cos}
+    float4* cell;
     float* cell_sun;            // [CH][CW] sum of sun shading
-    float* cell_shade;          // [CH][CW] sum of shade
 };
 struct SuperArgs {
     const int2* pix;            // pre-pass records [W4/4][H][4]
@@ -526,7 +527,6 @@ struct FeatArgs {
     int R;
     const float4* cell;
     const float* cell_sun;
-    const float* cell_shade;
     const float2* sup;
     const int2* range;
     const double* K64;
