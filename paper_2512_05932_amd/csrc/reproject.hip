@@ -2,13 +2,13 @@
 // footprint kernels read (section II-C: a pinhole image makes the kernel
 // inhomogeneous; reprojecting the rendered image restores one kernel for
 // all beams), with the renderer's depth decoded from a z buffer (section
-// II-D).  Threads along a row, each over kReprojRows rows of its column: the
+// II-D).  Threads along a row, each over a few rows of its column: the
 // six output planes are written coalesced; the reads gather the nearest
 // pinhole pixel, which neighbouring threads share.  The kernel is bound by
 // FP64 arithmetic, of which the directions' sines and cosines were the larger
 // part with a thread per pixel: now a column's are computed once per thread, a
 // row's once per workgroup.  4096 x 1024 pixels: 56 us with a thread per
-// pixel, 34 us now (100 MB written, 20 us at the rate of a copy).
+// pixel, 33 us now (100 MB written, 20 us at the rate of a copy).
 //
 // Contraction is off: the index and range decisions are plain IEEE FP64
 // operations in the order written, so that an output depth is the FP32
@@ -41,15 +41,19 @@ __device__ inline double decode_depth(const ReprojectArgs& a, long px)
     return a.z_near * a.z_far / (a.z_far - w * (a.z_far - a.z_near));
 }
 
-constexpr int kReprojRows = 8;
+// Rows of a workgroup: as many as leave four workgroups per CU.  Times in us
+// with 1, 2, 4 and 8: 4096 x 1024 pixels 42, 33, 29, 30; 2048 x 512 13.6, 12.1,
+// 12.0, 14.6; 1024 x 512 8.7, 7.8, 9.1, 11.0; 637 x 216 6.6, 6.6, 6.6, 9.9.
+constexpr int kReprojRows = 4;            // at most
+constexpr long kReprojGroups = 1024;
 
 __global__ __launch_bounds__(256)
-void k_reproject(ReprojectArgs a)
+void k_reproject(ReprojectArgs a, int rows)
 {
     __shared__ double2 row_cs[kReprojRows];               // cos, sin of the rows' elevations
-    const int u = blockIdx.x * blockDim.x + threadIdx.x, v0 = blockIdx.y * kReprojRows;
+    const int u = blockIdx.x * blockDim.x + threadIdx.x, v0 = blockIdx.y * rows;
     const double d2r = kPi / 180.0;
-    if (threadIdx.x < kReprojRows) {
+    if ((int)threadIdx.x < rows) {
         const double el = (a.el_max - ((double)(v0 + (int)threadIdx.x) + 0.5) * a.de) * d2r;
         row_cs[threadIdx.x] = make_double2(cos(el), sin(el));
     }
@@ -59,7 +63,7 @@ void k_reproject(ReprojectArgs a)
     if (u >= a.W) return;
     const double* R = a.rot;                              // row-major, camera -> sensor
 #pragma unroll 1
-    for (int v = v0; v < min(a.H, v0 + kReprojRows); ++v) {
+    for (int v = v0; v < min(a.H, v0 + rows); ++v) {
         const double ce = row_cs[v - v0].x;
         const double vs[3] = {ce * ca, ce * sa, row_cs[v - v0].y};
         // R^T v: the direction in the camera frame (x right, y down, z forward)
@@ -120,8 +124,11 @@ void k_reproject(ReprojectArgs a)
 
 hipError_t launch_reproject(hipStream_t s, const ReprojectArgs& a)
 {
-    dim3 grid((a.W + 255) / 256, (a.H + kReprojRows - 1) / kReprojRows);
-    hipLaunchKernelGGL(k_reproject, grid, dim3(256), 0, s, a);
+    const int cols = (a.W + 255) / 256;
+    int rows = kReprojRows;
+    while (rows > 1 && (long)cols * ((a.H + rows - 1) / rows) < kReprojGroups) rows /= 2;
+    dim3 grid(cols, (a.H + rows - 1) / rows);
+    hipLaunchKernelGGL(k_reproject, grid, dim3(256), 0, s, a, rows);
     return hipGetLastError();
 }
 
