@@ -868,20 +868,21 @@ void share_groups(FootprintArgs& a)
 }
 
 // Whether a single frame of B beams runs in the wave schedule: one histogram
-// slot per wave, waveforms short enough for registers, beams enough to fill
-// the chip with a wave each, and kernels so small that a wave's longer gather
-// costs less than a group's barriers.  Where groups hold one beam the bound on
-// the kernel's cells grows with the beams that hide a wave's latency; where
-// they share their pixels' reads it is fixed.  Frames with 512 bins, groups
-// against waves: 1000 beams of 20 samples 14.8 and 14.6 us, 2048 beams 20.8
-// and 19.5, 4000 beams 30.7 and 22.3; single beams of 400 samples: 2048 beams
-// 38 and 46 us, 4000 beams 47 and 40; of 1500 samples: 8000 beams 86 and 67;
-// shared: 8000 beams of 100 samples 51 and 31 us, of 400 samples 50 and 66.
+// slot per wave, waveforms short enough for registers, beams enough to hide
+// the latency of a wave's longer chain, and kernels so small that its gather
+// is short whatever the image holds (a step in which some lane's run ends
+// costs several times one in which none does).  Frames on 1024 x 512 pixels,
+// groups against waves: 512 bins, 1000 beams of 100 samples 15.9 and 18.2 us,
+// 2048 beams 23.4 and 20.9, 8000 beams 51 and 31; 2048 bins, 2048 beams 27.8
+// and 27.1 us, 8000 beams 65 and 44.  4000 beams of 400 samples 36 and 46 us
+// there, but 47 and 40 on 4096 x 1024 pixels, where runs are longer.  Not for
+// selections that need every run's key (they are not found as the waveform is
+// written): 17256 beams of 64 samples, strongest echo, 92 and 98 us.
 bool frame_in_waves(const FootprintArgs& a, size_t B)
 {
-    if (a.G != kWavesPerGroup || a.p.R > kWaveMaxBins || B < 2048) return false;
-    const size_t cells = (size_t)a.f.KW * a.f.KH;
-    return cells <= (B < 2 * (size_t)a.n_groups ? std::min<size_t>(B / 6, 2000) : 160);
+    constexpr int kCells = 160;                          // about 125 samples of a round footprint
+    if (a.p.select == LIDAR_ECHO_STRONGEST || a.p.select == LIDAR_ECHO_LONGEST) return false;
+    return a.G == kWavesPerGroup && a.p.R <= kWaveMaxBins && B >= 2048 && (long)a.f.KW * a.f.KH <= kCells;
 }
 
 PathDev path_view(const lidar_sim* h)

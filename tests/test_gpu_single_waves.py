@@ -14,7 +14,7 @@ import scenes
 pytestmark = pytest.mark.gpu
 
 # half extents in pixels
-KERNELS = {"narrow": (4, 3), "wide": (14, 11)}
+KERNELS = {"narrow": (4, 3), "wide": (6, 5)}
 
 
 @pytest.fixture(scope="module")
