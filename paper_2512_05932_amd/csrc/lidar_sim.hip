@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "engine.h"
+#include "routes.h"
 
 using namespace lidar;
 
@@ -2378,20 +2379,26 @@ lidar_status lidar_sim_surrogate_forward(lidar_sim* h, const void* x, float* y, 
 
 // Loss and gradients of the rows into `grads` and `loss`: by the kernels
 // themselves where these are device arrays that a kernel may write, else (or
-// null) into the handle's, from where they are copied.
+// null) into the handle's, from where they are copied.  The kernels clear both
+// and add to them before the last of them has read the rows and the labels, so
+// results that share memory with those or with each other are copied, too.
 static lidar_status sur_grads(lidar_sim* h, const void* x, const float* labels, uint32_t n, float* grads, float* loss)
 {
     LIDAR_TRY(sur_check(h, x, labels, n));
-    auto own = [](float* p, size_t count, float* ours) {
-        return p && (uintptr_t)p % sizeof(float) == 0 && device_range(p, count * sizeof(float)) ? p : ours;
+    constexpr size_t kGradBytes = (size_t)kSurParams * sizeof(float);
+    auto own = [&](float* p, size_t bytes, const float* other, size_t other_bytes, float* ours) {
+        const bool direct = p && (uintptr_t)p % sizeof(float) == 0 &&
+                            !ranges_overlap(p, bytes, x, (size_t)n * kSurIn * sizeof(uint16_t)) &&
+                            !ranges_overlap(p, bytes, labels, (size_t)n * kSurOut * sizeof(float)) &&
+                            !(other && ranges_overlap(p, bytes, other, other_bytes)) && device_range(p, bytes);
+        return direct ? p : ours;
     };
-    const size_t P = (size_t)kSurParams;
-    float* g = own(grads, P, h->net.grad.p);
-    float* l = own(loss, 1, h->work.loss.p);
+    float* g = own(grads, kGradBytes, loss, sizeof(float), h->net.grad.p);
+    float* l = own(loss, sizeof(float), grads, kGradBytes, h->work.loss.p);
     HIP_TRY(h, sur_gradients(h->stream, h->net, (const uint16_t*)x, labels, (long)n, h->work, g, l),
             "surrogate gradients");
     if (grads && g != grads)
-        HIP_TRY(h, hipMemcpyAsync(grads, g, P * sizeof(float), hipMemcpyDeviceToDevice, h->stream), "copy gradients");
+        HIP_TRY(h, hipMemcpyAsync(grads, g, kGradBytes, hipMemcpyDeviceToDevice, h->stream), "copy gradients");
     if (loss && l != loss)
         HIP_TRY(h, hipMemcpyAsync(loss, l, sizeof(float), hipMemcpyDeviceToDevice, h->stream), "copy loss");
     return LIDAR_OK;

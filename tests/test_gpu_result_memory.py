@@ -1,0 +1,88 @@
+"""Results written straight into the caller's device arrays: arrays that share memory with the call's inputs or with
+each other get what separate arrays get, in the order in which the header lists them."""
+import numpy as np
+import pytest
+
+import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lidar():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2512_05932_amd as lidar
+    lidar.load()
+    return lidar
+
+
+def _net(lidar, n, deterministic):
+    import torch
+    sim = lidar.LidarSim(scenes.iid_frame(0).params, stream=torch.cuda.current_stream(), deterministic=deterministic)
+    sim.set_weights(scenes.surrogate_init(3))
+    bits = scenes.random_bf16_bits(n, n, scale=1.0).view(np.int16)
+    return sim, bits, scenes.random_surrogate_labels(n + 1, n)
+
+
+@pytest.mark.parametrize("n", [64, 700])
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("shared", ["grads in rows", "loss in labels", "loss in rows", "loss in grads"])
+def test_gradients_share_memory_with_inputs(lidar, n, deterministic, shared):
+    """Fixed order of the sums: the same bits.  Shares added with atomics (n = 700: three of 256 rows): three partial
+    sums in any order differ by 3 * 2^-24 of their magnitudes, 1e-5 of the largest gradient bounds that."""
+    import torch
+    sim, bits, lab = _net(lidar, n, deterministic)
+    P = lidar._binding.SUR_PARAMS
+
+    def room():                                   # rows (or gradients), labels, loss
+        a = torch.zeros(max(n * 1056 // 2, P) + 16, dtype=torch.float32, device="cuda")
+        x = a.view(torch.int16)[:n * 1056].view(n, 1056)
+        x.copy_(torch.from_numpy(bits.copy()))
+        return a, x, torch.from_numpy(lab).cuda()
+    try:
+        _, x, lb = room()
+        g0, l0 = torch.full((P,), 7.0, device="cuda"), torch.full((1,), 7.0, device="cuda")
+        sim.surrogate_gradients(x, lb, g0, l0)
+        a, x, lb = room()
+        g, l = torch.full((P,), 7.0, device="cuda"), torch.full((1,), 7.0, device="cuda")
+        if shared == "grads in rows":
+            g = a[:P]
+        elif shared == "loss in labels":
+            l = lb.view(-1)[16 * (n - 1):16 * (n - 1) + 1]     # the last row's first existence label
+        elif shared == "loss in rows":
+            l = a[(n - 1) * 528:(n - 1) * 528 + 1]             # the last row's first inputs
+        else:
+            l = g[5:6]
+        sim.surrogate_gradients(x, lb, g, l)
+        want, loss = g0.cpu().numpy(), l0.item()
+        if shared == "loss in grads":
+            want[5] = loss
+        got = g.cpu().numpy()
+        tol = 0.0 if deterministic or n <= 256 else 1e-5 * np.abs(want).max()
+        if shared == "loss in grads":
+            assert got[5] == pytest.approx(loss, rel=1e-5)
+            got[5] = loss
+        assert np.abs(got - want).max() <= tol
+        assert l.item() == pytest.approx(loss, rel=1e-5)
+    finally:
+        sim.close()
+
+
+def test_training_loss_inside_labels(lidar):
+    import torch
+    n = 500
+    losses, thetas = [], []
+    for inside in (False, True):
+        sim, bits, lab = _net(lidar, n, True)
+        try:
+            x, lb = torch.from_numpy(bits.copy()).cuda(), torch.from_numpy(lab).cuda()
+            loss = lb.view(-1)[16 * (n - 1) + 1:16 * (n - 1) + 2] if inside else torch.zeros(1, device="cuda")
+            sim.train_step(x, lb, loss=loss)
+            losses.append(loss.item())
+            thetas.append(sim.get_weights())
+        finally:
+            sim.close()
+    np.testing.assert_array_equal(thetas[1], thetas[0])
+    assert losses[1] == pytest.approx(losses[0], rel=1e-5)
