@@ -930,16 +930,22 @@ bool device_range(const void* p, size_t bytes)
 }
 
 // The results into the caller's arrays: on the device one kernel on the
-// stream (arrays that it cannot take are copied one by one), to the host
-// copies and a synchronisation.
+// stream (arrays that it cannot take are copied one by one; so are all of them
+// where two overlap, so that the later one wins), to the host copies and a
+// synchronisation.
 lidar_status copy_outputs(lidar_sim* h, const Output (&out)[kOutSegments], bool device)
 {
     hipStream_t s = h->stream;
     OutSegments seg{};
+    bool apart = true;
+    for (int i = 0; i < kOutSegments; ++i)
+        for (int j = 0; j < i; ++j)
+            apart = apart && !(out[i].dst && out[j].dst &&
+                               ranges_overlap(out[i].dst, out[i].bytes, out[j].dst, out[j].bytes));
     for (int i = 0; i < kOutSegments; ++i) {
         const Output& o = out[i];
         if (!o.dst) continue;
-        if (device && device_range(o.dst, o.bytes) && out_segment(&seg.seg[i], o.dst, o.src, o.bytes)) continue;
+        if (device && apart && device_range(o.dst, o.bytes) && out_segment(&seg.seg[i], o.dst, o.src, o.bytes)) continue;
         HIP_TRY(h, hipMemcpyAsync(o.dst, o.src, o.bytes,
                                   device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s), o.what);
     }

@@ -86,3 +86,40 @@ def test_training_loss_inside_labels(lidar):
             sim.close()
     np.testing.assert_array_equal(thetas[1], thetas[0])
     assert losses[1] == pytest.approx(losses[0], rel=1e-5)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_overlapping_destinations_are_written_in_order(lidar, batch):
+    """Echoes, counts, waveforms, beam records: where two destinations overlap, the later one's bytes stay."""
+    import torch
+    w = scenes.iid_frame(1)
+    az, el = scenes.grid_beams(w.gbuffer.raster, 64, 32)
+    pat = scenes.Pattern(scenes.PATTERN_GAUSS, az, el, sigma_deg=(0.1, 0.1), trunc_sigmas=3.0)
+    planes = lidar.upload_gbuffer(w.gbuffer, "cuda")
+    sim = lidar.LidarSim(w.params, stream=torch.cuda.current_stream(), keep_waveforms=True)
+    try:
+        if batch:
+            sim.simulate_batch(lidar.Batch([(w.gbuffer.raster, planes)], [pat]))
+            want = sim.read_batch(0, waveforms=True)
+        else:
+            sim.set_pattern(pat)
+            sim.set_gbuffer(w.gbuffer.raster, planes)
+            sim.simulate_frame()
+            want = sim.read(waveforms=True)
+        parts = [want[k].view(np.uint8).ravel() for k in ("echoes", "n_echoes", "waveforms", "beams")]
+        # each begins 64 bytes after the one before it, the longest (waveforms) among them
+        at = [0, 64, 128, 192]
+        size = max(o + len(b) for o, b in zip(at, parts))
+        ref = np.zeros(size, np.uint8)
+        for o, b in zip(at, parts):
+            ref[o:o + len(b)] = b
+        for _ in range(5):
+            room = torch.zeros(size, dtype=torch.uint8, device="cuda")
+            p = [room.data_ptr() + o for o in at]
+            lib = lidar.load()
+            rc = lib.lidar_sim_read_batch(sim._h, 0, *p, 1) if batch else lib.lidar_sim_read_echoes(sim._h, *p, 1)
+            assert rc == lidar.LIDAR_OK
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(room.cpu().numpy(), ref)
+    finally:
+        sim.close()
