@@ -100,6 +100,7 @@ struct lidar_sim {
     int G = 4;                         // beams per group (LDS budget)
     DevBuf<float> d_taps;
 
+    int device = -1;                   // device current at create, if the stream is one of it (else -1)
     int cus = 256;                     // compute units of the device (queried at create)
     size_t lds_max = 65536;            // LDS of a workgroup on the device (queried at create)
 
@@ -911,17 +912,17 @@ struct Output {
     const char* what;
 };
 
-// Whether [p, p + bytes) is memory of the current device inside one
-// allocation, which a kernel may write (anything else goes to the copy
-// engine, which checks its ranges and reaches other devices and the host).
-bool device_range(const void* p, size_t bytes)
+// Whether [p, p + bytes) is memory of the handle's device inside one
+// allocation, which a kernel on its stream may write (anything else goes to the
+// copy engine, which checks its ranges and reaches other devices and the host).
+bool device_range(const lidar_sim* h, const void* p, size_t bytes)
 {
     hipPointerAttribute_t at{};
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
     int dev = 0;
     if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
-        hipGetDevice(&dev) != hipSuccess || at.device != dev ||
+        hipGetDevice(&dev) != hipSuccess || !one_device(at.device, h->device, dev) ||
         hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
         return false;
@@ -945,7 +946,7 @@ lidar_status copy_outputs(lidar_sim* h, const Output (&out)[kOutSegments], bool 
     for (int i = 0; i < kOutSegments; ++i) {
         const Output& o = out[i];
         if (!o.dst) continue;
-        if (device && apart && device_range(o.dst, o.bytes) && out_segment(&seg.seg[i], o.dst, o.src, o.bytes)) continue;
+        if (device && apart && device_range(h, o.dst, o.bytes) && out_segment(&seg.seg[i], o.dst, o.src, o.bytes)) continue;
         HIP_TRY(h, hipMemcpyAsync(o.dst, o.src, o.bytes,
                                   device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s), o.what);
     }
@@ -1761,7 +1762,11 @@ lidar_status lidar_sim_create(const lidar_sim_params* params, void* hip_stream, 
     h->prm = *params;
     h->stream = (hipStream_t)hip_stream;
     {
-        int dev = 0, n = 0, l = 0;
+        int dev = 0, on = 0, n = 0, l = 0;
+        if (hipGetDevice(&dev) == hipSuccess && hipStreamGetDevice(h->stream, &on) == hipSuccess && on == dev)
+            h->device = dev;
+        else
+            (void)hipGetLastError();
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
             h->cus = n;
@@ -2396,7 +2401,7 @@ static lidar_status sur_grads(lidar_sim* h, const void* x, const float* labels, 
         const bool direct = p && (uintptr_t)p % sizeof(float) == 0 &&
                             !ranges_overlap(p, bytes, x, (size_t)n * kSurIn * sizeof(uint16_t)) &&
                             !ranges_overlap(p, bytes, labels, (size_t)n * kSurOut * sizeof(float)) &&
-                            !(other && ranges_overlap(p, bytes, other, other_bytes)) && device_range(p, bytes);
+                            !(other && ranges_overlap(p, bytes, other, other_bytes)) && device_range(h, p, bytes);
         return direct ? p : ours;
     };
     float* g = own(grads, kGradBytes, loss, sizeof(float), h->net.grad.p);

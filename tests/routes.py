@@ -1,0 +1,32 @@
+"""The engine's host rules (csrc/routes.h), compiled by themselves as plain C++ for the tests."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = """
+#include "routes.h"
+extern "C" {
+int ranges_overlap(const void* p, size_t pn, const void* q, size_t qn) { return lidar::ranges_overlap(p, pn, q, qn); }
+int one_device(int memory, int handle, int current) { return lidar::one_device(memory, handle, current); }
+}
+"""
+
+_lib = None
+
+
+def load():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "rules.cpp"), os.path.join(d, "librules.so")
+            with open(src, "w") as f:
+                f.write(SOURCE)
+            inc = [os.path.join(ROOT, "paper_2512_05932_amd", "csrc"), os.path.join(ROOT, "include")]
+            subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", *[f"-I{i}" for i in inc], src, "-o", so],
+                           check=True)
+            _lib = C.CDLL(so)
+        _lib.ranges_overlap.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t]
+    return _lib
