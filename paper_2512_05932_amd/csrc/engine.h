@@ -17,6 +17,7 @@ constexpr int kMaxTaps = 257;
 constexpr int kPassBins = 2048;                 // bins per convolution pass (8 per thread)
 constexpr int kMaxEchoes = 8;                   // largest max_echoes
 constexpr int kWaveMaxBins = 2048;              // longest waveform of the wave schedule (in registers)
+constexpr int kWavePassBins = 512;              // bins of one of its output passes
 // chunks of 1 << chunk_shift(R) bins (at least 64) cover R bins with at most 32
 __host__ __device__ constexpr int chunk_shift(int R)
 {

@@ -890,7 +890,6 @@ __device__ inline void wave_sync()
 }
 
 // The wave schedule's convolution runs in passes of 512 bins (8 per lane).
-constexpr int kWavePassBins = 512;
 constexpr int kWavePasses = kWaveMaxBins / kWavePassBins;
 
 // Lanes below this one with their bit set in m.

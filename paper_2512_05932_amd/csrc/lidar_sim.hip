@@ -869,22 +869,29 @@ void share_groups(FootprintArgs& a)
     a.chunk = (a.n_groups + kXcds * a.band - 1) / (kXcds * a.band) * a.band;
 }
 
-// Whether a single frame of B beams runs in the wave schedule: one histogram
-// slot per wave, waveforms short enough for registers, beams enough to hide
-// the latency of a wave's longer chain, and kernels so small that its gather
-// is short whatever the image holds (a step in which some lane's run ends
-// costs several times one in which none does).  Frames on 1024 x 512 pixels,
-// groups against waves: 512 bins, 1000 beams of 100 samples 15.9 and 18.2 us,
-// 2048 beams 23.4 and 20.9, 8000 beams 51 and 31; 2048 bins, 2048 beams 27.8
-// and 27.1 us, 8000 beams 65 and 44.  4000 beams of 400 samples 36 and 46 us
-// there, but 47 and 40 on 4096 x 1024 pixels, where runs are longer.  Not for
-// selections that need every run's key (they are not found as the waveform is
-// written): 17256 beams of 64 samples, strongest echo, 92 and 98 us.
-bool frame_in_waves(const FootprintArgs& a, size_t B)
+// Workgroups of the group kernel that a CU holds at the LDS-bound occupancy.
+size_t groups_per_cu(int G, int R, int J)
 {
-    constexpr int kCells = 160;                          // about 125 samples of a round footprint
-    if (a.p.select == LIDAR_ECHO_STRONGEST || a.p.select == LIDAR_ECHO_LONGEST) return false;
-    return a.G == kWavesPerGroup && a.p.R <= kWaveMaxBins && B >= 2048 && (long)a.f.KW * a.f.KH <= kCells;
+    const size_t lds = group_lds_bytes(G, R, J) + 2048;      // + static LDS
+    return std::max<size_t>(1, std::min<size_t>(8, (160 * 1024) / lds));
+}
+
+// Whether a single frame of B beams runs in the wave schedule: groups of a
+// histogram slot per wave, waveforms short enough for registers (one pass: eight
+// workgroups per CU, else four), and a frame for which it is the faster one.
+bool frame_in_waves(const FootprintArgs& a, size_t B, uint32_t range_mode)
+{
+    if (a.G != kWavesPerGroup || a.p.R > kWaveMaxBins) return false;
+    FrameShape f;
+    f.beams = (long)B;
+    f.groups = a.n_groups;
+    f.kernel_w = a.f.KW;
+    f.kernel_h = a.f.KH;
+    f.select = (uint32_t)a.p.select;
+    f.range_mode = range_mode;
+    f.held = (int)groups_per_cu(a.G, a.p.R, a.p.J);
+    f.held_wave = a.p.R <= kWavePassBins ? 8 : 4;
+    return frame_in_waves(f);
 }
 
 PathDev path_view(const lidar_sim* h)
@@ -1410,8 +1417,7 @@ lidar_status setup_batch(lidar_sim* h, const lidar_gbuffer_desc* gbs, const lida
     // persistent grid: as many workgroups as the CUs hold at the LDS-bound
     // occupancy (extra workgroups would find the queue empty and exit); the
     // wave schedule's: those that are resident, an item per wave at most
-    const size_t lds = group_lds_bytes(G, R, h->J) + 2048;   // + static LDS
-    const size_t per_cu = std::max<size_t>(1, std::min<size_t>(8, (160 * 1024) / lds));
+    const size_t per_cu = groups_per_cu(G, (int)R, h->J);
     h->b_grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)h->cus * per_cu, total_groups));
     h->b_grid_wave = 1;
     if (wave_schedule_ok(h)) {
@@ -1732,7 +1738,8 @@ lidar_status simulate_static(const lidar_sim_params* prm, const lidar_pattern_de
     fa.n_groups = fs.n_groups;
     fa.G = G;
     share_groups(fa);
-    HIP_TRY(h, frame_in_waves(fa, B) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa), "footprint launch");
+    HIP_TRY(h, frame_in_waves(fa, B, prm->range_mode) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa),
+            "footprint launch");
     return LIDAR_OK;
 }
 
@@ -2089,7 +2096,8 @@ lidar_status lidar_sim_simulate_frame(lidar_sim* h, uint32_t mode)
     if (corr || det)
         HIP_TRY(h, launch_footprint_one(s, fa, corr, det), "footprint launch");
     else
-        HIP_TRY(h, frame_in_waves(fa, B) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa), "footprint launch");
+        HIP_TRY(h, frame_in_waves(fa, B, h->prm.range_mode) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa),
+                "footprint launch");
     if (prof) {
         HIP_TRY(h, hipEventRecord(fp.b, s), "record event");
         h->pending_pp.push_back(pp);
@@ -2194,8 +2202,7 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     ba.n_items_dev = h->s_cnt.p;
     ba.tickets = nullptr;
     ba.n_tickets = 0;
-    const size_t lds = group_lds_bytes(h->G, (int)R, h->J) + 2048;   // + static LDS
-    const size_t per_cu = std::max<size_t>(1, std::min<size_t>(8, (160 * 1024) / lds));
+    const size_t per_cu = groups_per_cu(h->G, (int)R, h->J);
     const int grid = (int)std::max<size_t>(1, std::min<size_t>((size_t)h->cus * per_cu, (size_t)fs.n_groups));
     HIP_TRY(h, launch_footprint_batch(s, ba, grid, h->prm.sun_irradiance != 0.0, keep),
             "fallback footprint launch");

@@ -5,6 +5,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "../../include/lidar_sim.h"
+
 namespace lidar {
 
 // Whether [p, p + pn) and [q, q + qn) share a byte.
@@ -21,6 +23,50 @@ inline bool ranges_overlap(const void* p, size_t pn, const void* q, size_t qn)
 inline bool one_device(int memory, int handle, int current)
 {
     return handle >= 0 && memory == handle && current == handle;
+}
+
+// Whether a single frame whose groups hold up to four beams runs with a wave per
+// group (which takes the group's beams one after another) instead of a
+// workgroup per group.  A beam takes the wave longer, so there have to be
+// several times as many groups as workgroups resident on the chip: `held` per
+// CU of the group kernel (by its LDS), `held_wave` per CU of the wave kernel.
+//
+// Measured over 2304 frames (2048 to 32000 beams in grids, rows and Lissajous
+// figures; 512, 1200 and 2048 bins; i.i.d. surfaces, a road and a flat wall on
+// 1024 x 512 and 4096 x 1024 pixels).  The frames that the rule sends to the
+// waves take 0.64 of the time on average and 1.01 of it at most.  Left to
+// the groups, with their times (groups, waves):
+//  * few groups: 2048 single beams of a 9 x 7 kernel 24.6 and 36.9 us;
+//  * full groups, whose pixels the workgroup reads once: 24000 beams of a 9 x 7
+//    kernel in 6000 groups (2048 bins) 1.09 of the time;
+//  * 513 to some 1600 bins, where a CU holds more groups: 6504 beams of a 9 x 7
+//    kernel, 1200 bins, 40.9 and 47.9 us;
+//  * long kernels, whose rows or columns the wave walks alone: 4000 beams of a
+//    1 x 141 kernel 38.5 and 51.1 us; kernels of more than 160 cells: 4000 beams
+//    of 400 samples 36 and 46 us;
+//  * range intervals, a step per bin of a pixel's range: 8000 beams of an 11 x 11
+//    kernel 93 and 240 us (2048 bins);
+//  * selections that need every run's key, which are not found as the waveform
+//    is written: 17256 beams of 64 samples, strongest echo, 92 and 98 us.
+struct FrameShape {
+    long beams, groups;
+    int kernel_w, kernel_h;
+    uint32_t select, range_mode;    // LIDAR_ECHO_*, LIDAR_RANGE_*
+    int held, held_wave;
+};
+
+inline bool frame_in_waves(const FrameShape& f)
+{
+    constexpr long kCells = 160;
+    constexpr int kRound = 13, kLong = 41;
+    if (f.select == LIDAR_ECHO_STRONGEST || f.select == LIDAR_ECHO_LONGEST) return false;
+    if (f.range_mode != LIDAR_RANGE_CENTRE || f.groups <= 0) return false;
+    const int extent = f.kernel_w > f.kernel_h ? f.kernel_w : f.kernel_h;
+    if ((long)f.kernel_w * f.kernel_h > kCells || extent > kLong) return false;
+    const double per_group = (double)f.beams / (double)f.groups;
+    double need = 3500.0 + 1000.0 * per_group + (extent > kRound ? 2000.0 : 0.0);
+    if (f.held > f.held_wave) need = need * f.held / f.held_wave;
+    return (double)f.groups >= need;
 }
 
 }  // namespace lidar

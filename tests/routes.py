@@ -11,6 +11,10 @@ SOURCE = """
 extern "C" {
 int ranges_overlap(const void* p, size_t pn, const void* q, size_t qn) { return lidar::ranges_overlap(p, pn, q, qn); }
 int one_device(int memory, int handle, int current) { return lidar::one_device(memory, handle, current); }
+int in_waves(long beams, long groups, int kw, int kh, unsigned select, unsigned range_mode, int held, int held_wave)
+{
+    return lidar::frame_in_waves(lidar::FrameShape{beams, groups, kw, kh, select, range_mode, held, held_wave});
+}
 }
 """
 
@@ -28,5 +32,10 @@ def load():
             subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", *[f"-I{i}" for i in inc], src, "-o", so],
                            check=True)
             _lib = C.CDLL(so)
+        _lib.in_waves.argtypes = [C.c_long, C.c_long, C.c_int, C.c_int, C.c_uint, C.c_uint, C.c_int, C.c_int]
         _lib.ranges_overlap.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t]
     return _lib
+
+
+def in_waves(beams, groups, kernel_w, kernel_h, select, range_mode, held, held_wave) -> bool:
+    return bool(load().in_waves(beams, groups, kernel_w, kernel_h, select, range_mode, held, held_wave))

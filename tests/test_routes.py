@@ -1,6 +1,8 @@
 """Host rules that choose between two ways of doing the same call."""
 import itertools
 
+import pytest
+
 from . import routes
 
 
@@ -20,3 +22,29 @@ def test_a_kernel_writes_only_memory_of_the_one_device():
     r = routes.load()
     for memory, handle, current in itertools.product((0, 1), (-1, 0, 1), (0, 1)):
         assert bool(r.one_device(memory, handle, current)) == (memory == handle == current)
+
+
+# beams, groups, kernel, echo selection, range mode, groups held per CU, wave workgroups held per CU
+@pytest.mark.parametrize("frame,waves", [
+    ((32000, 16000, 11, 11, 0, 0, 4, 4), True),       # a pinhole camera's frame
+    ((5000, 4688, 11, 11, 0, 0, 4, 4), True),         # a stateless frame
+    ((9000, 9000, 13, 12, 2, 0, 8, 8), True),
+    ((9000, 9000, 13, 12, 5, 0, 8, 8), True),
+    # each of these was slower by the wave (1.06 to 2.6 times)
+    ((2048, 1978, 9, 7, 0, 0, 8, 8), False),          # few groups
+    ((4000, 3478, 9, 7, 0, 0, 8, 8), False),
+    ((4000, 1000, 9, 7, 0, 0, 8, 8), False),          # full groups
+    ((24000, 6000, 9, 7, 0, 0, 4, 4), False),
+    ((6504, 5636, 9, 7, 0, 0, 7, 4), False),          # many groups resident per CU (1200 bins)
+    ((32000, 8000, 9, 7, 0, 0, 7, 4), False),
+    ((8000, 6278, 1, 141, 0, 0, 4, 4), False),        # long kernels
+    ((8000, 2897, 141, 1, 0, 0, 8, 8), False),
+    ((8000, 5282, 21, 7, 0, 0, 4, 4), False),
+    ((8000, 8000, 11, 11, 0, 2, 4, 4), False),        # range intervals
+    ((17256, 17256, 9, 7, 1, 0, 8, 8), False),        # every run's key: strongest, longest
+    ((17256, 17256, 9, 7, 3, 0, 8, 8), False),
+    ((32000, 32000, 13, 13, 0, 0, 8, 8), False),      # more than 160 cells
+    ((0, 0, 1, 1, 0, 0, 8, 8), False),
+])
+def test_frames_in_waves(frame, waves):
+    assert routes.in_waves(*frame) == waves
