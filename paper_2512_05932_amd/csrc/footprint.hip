@@ -1485,6 +1485,13 @@ __device__ inline int group_of(int x, int i, int band)
     return (q * kXcds + x) * band + (i - q * band);
 }
 
+// The same for a workgroup per group on a grid of kXcds band x bands (workgroups
+// go to the XCDs in turn along x, and kXcds divides a row).
+__device__ inline int group_of_block(int band)
+{
+    return (blockIdx.y * kXcds + blockIdx.x % kXcds) * band + blockIdx.x / kXcds;
+}
+
 template <int G, bool SUN, bool KEEP>
 __global__ __launch_bounds__(kFootprintThreads)
 void k_footprint(FootprintArgs a)
@@ -1498,10 +1505,10 @@ void k_footprint(FootprintArgs a)
     __shared__ unsigned amask[G][kMaxBins / kPassBins + 1];
 
     // XCD-aware schedule: workgroups go round-robin over the 8 XCDs, so slot
-    // s runs on XCD s % 8; each XCD takes one contiguous run of the
-    // spatially ordered groups, and the groups in flight on it share their
-    // pixels in its L2.
-    const int gi = group_of(blockIdx.x % kXcds, blockIdx.x / kXcds, a.band);
+    // s runs on XCD s % 8; each XCD takes one or a few bands of consecutive
+    // ones of the spatially ordered groups, and the groups in flight on it share
+    // their pixels in its L2.
+    const int gi = group_of_block(a.band);
     if (gi >= a.n_groups) return;
     const int tid = threadIdx.x;
     clear_group(lds4, G * RS / 4, &nzmask, tid);
@@ -1526,7 +1533,7 @@ void k_footprint_one(FootprintArgs a)
     __shared__ float red[1][kWaves];
     __shared__ unsigned nzmask;
     __shared__ unsigned amask[1][kMaxBins / kPassBins + 1];
-    const int gi = group_of(blockIdx.x % kXcds, blockIdx.x / kXcds, a.band);
+    const int gi = group_of_block(a.band);
     if (gi >= a.n_groups) return;
     const int tid = threadIdx.x;
     clear_group(lds4, S * RS / 4, &nzmask, tid);
@@ -1786,7 +1793,7 @@ __global__ void k_reset_queue(int* counter, int n)
 template <int G>
 static hipError_t launch_g(hipStream_t s, const FootprintArgs& a)
 {
-    const int grid = kXcds * a.chunk;
+    const dim3 grid(kXcds * a.band, a.chunk / a.band);
     const size_t lds = group_lds_bytes(G, a.p.R, a.p.J);
     const bool sun = a.f.sun != nullptr && !a.f.floor_given;   // a supplied floor needs no sun sum
     const bool keep = a.f.waves != nullptr;
@@ -1903,7 +1910,7 @@ hipError_t launch_footprint_batch_wave(hipStream_t s, const BatchArgs& a, int gr
 template <bool CORR, bool DET>
 static hipError_t launch_one(hipStream_t s, const FootprintArgs& a)
 {
-    const int grid = kXcds * a.chunk;
+    const dim3 grid(kXcds * a.band, a.chunk / a.band);
     const size_t lds = group_lds_bytes(DET ? kWaves : 1, a.p.R, a.p.J);
     const bool sun = a.f.sun != nullptr && !a.f.floor_given, keep = a.f.waves != nullptr;
     if (sun && keep)

@@ -855,18 +855,12 @@ FrameDev frame_view(const lidar_sim* h, const FrameState& fs, lidar_beam_info* b
     return f;
 }
 
-// Share a frame's groups out to the XCDs: bands of consecutive groups (they are
-// in column order, so a band's pixels stay in one L2), several per XCD, since
-// columns differ in cost and workgroups go to the XCDs in turn, whatever these
-// have left.  Times in us for one band per XCD, 4, 8, 16 and 64: 28800 beams
-// of 83000 samples 798, 751, 779, 792, 897; 14400 beams of 21000 corrected
-// samples 827, 688, 686, 652, 647; 32000 beams of 105 samples 141, 136, 132,
-// 133, 150; 15872 beams on 368 x 487 pixels 76, 71, 69, 69, 69.
-void share_groups(FootprintArgs& a)
+// Share a frame's groups out to the XCDs in bands of consecutive ones.
+void share_groups(FootprintArgs& a, bool corrected)
 {
-    constexpr int kBands = 8 * kXcds;
-    a.band = std::max(1, (a.n_groups + kBands - 1) / kBands);
-    a.chunk = (a.n_groups + kXcds * a.band - 1) / (kXcds * a.band) * a.band;
+    const XcdShare s = xcd_share(a.n_groups, (long)a.f.KW * a.f.KH, corrected, kXcds);
+    a.band = s.band;
+    a.chunk = s.chunk;
 }
 
 // Workgroups of the group kernel that a CU holds at the LDS-bound occupancy.
@@ -1737,7 +1731,7 @@ lidar_status simulate_static(const lidar_sim_params* prm, const lidar_pattern_de
     fa.groups = groups;
     fa.n_groups = fs.n_groups;
     fa.G = G;
-    share_groups(fa);
+    share_groups(fa, false);
     HIP_TRY(h, frame_in_waves(fa, B, prm->range_mode) ? launch_footprint_wave(s, fa) : launch_footprint(s, fa),
             "footprint launch");
     return LIDAR_OK;
@@ -2074,7 +2068,7 @@ lidar_status lidar_sim_simulate_frame(lidar_sim* h, uint32_t mode)
     fa.groups = h->d_groups.p;
     fa.n_groups = fs.n_groups;
     fa.G = h->G;
-    share_groups(fa);
+    share_groups(fa, h->prm.range_mode == LIDAR_RANGE_CORRECTED);
 
     EventPair pp{}, fp{};
     if (prof) {

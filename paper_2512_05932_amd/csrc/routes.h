@@ -55,18 +55,51 @@ struct FrameShape {
     int held, held_wave;
 };
 
+constexpr long kNarrowCells = 160;
+
 inline bool frame_in_waves(const FrameShape& f)
 {
-    constexpr long kCells = 160;
     constexpr int kRound = 13, kLong = 41;
     if (f.select == LIDAR_ECHO_STRONGEST || f.select == LIDAR_ECHO_LONGEST) return false;
     if (f.range_mode != LIDAR_RANGE_CENTRE || f.groups <= 0) return false;
     const int extent = f.kernel_w > f.kernel_h ? f.kernel_w : f.kernel_h;
-    if ((long)f.kernel_w * f.kernel_h > kCells || extent > kLong) return false;
+    if ((long)f.kernel_w * f.kernel_h > kNarrowCells || extent > kLong) return false;
     const double per_group = (double)f.beams / (double)f.groups;
     double need = 3500.0 + 1000.0 * per_group + (extent > kRound ? 2000.0 : 0.0);
     if (f.held > f.held_wave) need = need * f.held / f.held_wave;
     return (double)f.groups >= need;
+}
+
+// Bands of consecutive groups that an XCD takes of a frame.  Groups are in
+// column order, so one band per XCD keeps the most pixels in its L2, but columns
+// differ in cost, and workgroups go to the XCDs in turn, whatever these have
+// left.  Times in us with 1, 2, 4 and 8 bands: 28800 beams of 83000 samples 932,
+// 831, 756, 772; 14400 beams of 21000 corrected samples, which read less for their
+// FP64 arithmetic, 888, 796, 779, 750 (another scene 1010, 796, 727, 729); 32000
+// beams of 105 samples (in waves) 141, 140, 135, 133.  Frames of few groups are
+// on the chip at once and only lose: 7001 beams of 729 samples in 3330 groups
+// 47.0, 48.8, 50.0, 49.6.  Over 378 frames of 289 to 9801 cells, 1 to 20000 beams,
+// four bands from 4000 groups on take 0.985 of the time with one band (1.03 at
+// most, surfaces of even cost; 0.76 at least, a road under a sky); eight bands in
+// every frame took up to 1.10.  Frames of narrow kernels gain from 8000 groups
+// on: 0.965 to 0.98, where fewer groups take up to 1.10.
+inline int xcd_bands(long groups, long cells, bool corrected)
+{
+    if (groups < (cells > kNarrowCells ? 4000 : 8000)) return 1;
+    return corrected ? 8 : 4;
+}
+
+// Groups of a band, and of an XCD's bands together (its last ones may lie past
+// the frame's groups).
+struct XcdShare {
+    int band, chunk;
+};
+
+inline XcdShare xcd_share(int groups, long cells, bool corrected, int xcds)
+{
+    const int bands = xcd_bands(groups, cells, corrected);
+    const int band = groups > 0 ? (groups - 1) / (xcds * bands) + 1 : 1;
+    return {band, groups > 0 ? ((groups - 1) / (xcds * band) + 1) * band : 0};
 }
 
 }  // namespace lidar

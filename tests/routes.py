@@ -11,6 +11,12 @@ SOURCE = """
 extern "C" {
 int ranges_overlap(const void* p, size_t pn, const void* q, size_t qn) { return lidar::ranges_overlap(p, pn, q, qn); }
 int one_device(int memory, int handle, int current) { return lidar::one_device(memory, handle, current); }
+int xcd_share(int groups, long cells, int corrected, int* chunk)
+{
+    const lidar::XcdShare s = lidar::xcd_share(groups, cells, corrected != 0, 8);
+    *chunk = s.chunk;
+    return s.band;
+}
 int in_waves(long beams, long groups, int kw, int kh, unsigned select, unsigned range_mode, int held, int held_wave)
 {
     return lidar::frame_in_waves(lidar::FrameShape{beams, groups, kw, kh, select, range_mode, held, held_wave});
@@ -33,9 +39,16 @@ def load():
                            check=True)
             _lib = C.CDLL(so)
         _lib.in_waves.argtypes = [C.c_long, C.c_long, C.c_int, C.c_int, C.c_uint, C.c_uint, C.c_int, C.c_int]
+        _lib.xcd_share.argtypes = [C.c_int, C.c_long, C.c_int, C.POINTER(C.c_int)]
         _lib.ranges_overlap.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t]
     return _lib
 
 
 def in_waves(beams, groups, kernel_w, kernel_h, select, range_mode, held, held_wave) -> bool:
     return bool(load().in_waves(beams, groups, kernel_w, kernel_h, select, range_mode, held, held_wave))
+
+
+def xcd_share(groups, cells, corrected=False):
+    """Groups of a band and of an XCD."""
+    chunk = C.c_int()
+    return load().xcd_share(groups, cells, corrected, C.byref(chunk)), chunk.value
