@@ -448,7 +448,7 @@ hipError_t blas_gemm(BlasCtx* c, hipStream_t s, const GemmArgs& g);
 hipError_t launch_bias_gelu(hipStream_t s, const float* Z, const float* bias, uint16_t* H, long n, int C,
                             float* zero = nullptr, long zn = 0, float* loss = nullptr);
 hipError_t launch_loss(hipStream_t s, const float* Y, const float* bias, const float* lab, long n, uint16_t* dYb,
-                       float* loss_sum);
+                       float* loss_sum, bool det = false);
 hipError_t launch_gelu_back(hipStream_t s, const float* dH, const float* Z, const float* bias, uint16_t* dZb, long n,
                             int C);
 // dW = A^T D and db = column sums of D for the four layers; a workgroup takes

@@ -151,11 +151,13 @@ __device__ inline float sigm(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 // Per-row loss and gradient (scaled by 1/n) with respect to the 16 outputs Y +
 // bias; a wave per 64 rows (4096 rows then take 64 CUs and not 16: 7 us of
-// dependent exponentials and logarithms become 5).
-__global__ __launch_bounds__(64)
+// dependent exponentials and logarithms become 5), four waves together in the
+// deterministic mode, so that up to 256 rows are summed in a fixed order.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES)
 void k_loss(const float* Y, const float* bias, const float* lab, long n, float inv_n, uint16_t* dYb, float* loss_sum)
 {
-    const long r = (long)blockIdx.x * 64 + threadIdx.x;
+    const long r = (long)blockIdx.x * (64 * WAVES) + threadIdx.x;
     float L = 0.0f;
     if (r < n) {
         const float* l = lab + r * 16;
@@ -189,9 +191,17 @@ void k_loss(const float* Y, const float* bias, const float* lab, long n, float i
 #pragma unroll
         for (int j = 0; j < 16; ++j) dYb[r * 16 + j] = to_bf16(d[j] * inv_n);
     }
-    // the wave's sum of the row losses, one atomic
+    // the workgroup's sum of the row losses, one atomic
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) L += __shfl_xor(L, m);
+    if constexpr (WAVES > 1) {
+        __shared__ float part[WAVES];
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = L;
+        __syncthreads();
+        L = part[0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) L += part[w];
+    }
     if (threadIdx.x == 0) atomicAdd(loss_sum, L * inv_n);
 }
 
@@ -647,11 +657,14 @@ hipError_t launch_bias_gelu(hipStream_t s, const float* Z, const float* bias, ui
 }
 
 hipError_t launch_loss(hipStream_t s, const float* Y, const float* bias, const float* lab, long n, uint16_t* dYb,
-                       float* loss_sum)
+                       float* loss_sum, bool det)
 {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_loss, dim3(blocks(n, 64)), dim3(64), 0, s, Y, bias, lab, n, 1.0f / (float)n, dYb,
-                       loss_sum);
+    const float inv_n = 1.0f / (float)n;
+    if (det)
+        hipLaunchKernelGGL(k_loss<4>, dim3(blocks(n, 256)), dim3(256), 0, s, Y, bias, lab, n, inv_n, dYb, loss_sum);
+    else
+        hipLaunchKernelGGL(k_loss<1>, dim3(blocks(n, 64)), dim3(64), 0, s, Y, bias, lab, n, inv_n, dYb, loss_sum);
     return hipGetLastError();
 }
 
@@ -820,7 +833,7 @@ hipError_t sur_gradients(hipStream_t s, SurNet& net, const uint16_t* X, const fl
     const float* th = net.theta.p;
     const long span = weight_grad_span(n, net.det);
     TRY(sur_forward(s, net, X, n, w, span < n ? g : nullptr, loss));
-    TRY(launch_loss(s, w.Y.p, th + kSurOffB4, lab, n, w.dYb.p, loss));
+    TRY(launch_loss(s, w.Y.p, th + kSurOffB4, lab, n, w.dYb.p, loss, net.det));
     TRY(input_grad(s, w.dYb.p, kSurOut, Wb + kSurOffW4, kSurHid, n, w.dH.p, net.det, w.blas));
     TRY(launch_gelu_back(s, w.dH.p, w.Z3.p, th + kSurOffB3, w.dZ3.p, n, kSurHid));
     TRY(input_grad(s, w.dZ3.p, kSurHid, Wb + kSurOffW3, kSurHid, n, w.dH.p, net.det, w.blas));
