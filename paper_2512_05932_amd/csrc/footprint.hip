@@ -1333,9 +1333,9 @@ __device__ inline void clear_passes(float* hist, int R, unsigned dirty, unsigned
 // were written, bit 16 + ps for a quiet pass of which only the first and last
 // bins were (ALL and NEAREST with the floor at or below T: such a pass is the
 // floor throughout, holds no run, and only its edge bins can be read, as the
-// crossings of runs in the neighbouring passes).
-
-template <int NP, bool SUN, bool KEEP, bool FX = (NP > 1)>
+// crossings of runs in the neighbouring passes).  RANK: selections that rank
+// every run by a key (STRONGEST, LONGEST) may be asked for.
+template <int NP, bool SUN, bool KEEP, bool FX = (NP > 1), bool RANK = true>
 __device__ __attribute__((always_inline)) inline int process_beam_wave(
     const FrameDev& f, const PathDev& p, int beam, float* hist, int RS, const float* taps, unsigned* nzw,
     unsigned* am, int lane, unsigned long long* rk, int2* rb)
@@ -1415,7 +1415,7 @@ __device__ __attribute__((always_inline)) inline int process_beam_wave(
     for (int ps = 0; ps < NP; ++ps)
         conv_out8(hist, taps, p, nb, ps * kWavePassBins + lane * 8, nzm, nzs, o[ps]);
     // the first runs are found as the passes are written (ALL, NEAREST)
-    const bool first = p.select == LIDAR_ECHO_ALL || p.select == LIDAR_ECHO_NEAREST;
+    const bool first = !RANK || p.select == LIDAR_ECHO_ALL || p.select == LIDAR_ECHO_NEAREST;
     RunScan rs{p.select == LIDAR_ECHO_ALL ? p.E : 1, 0, 0u};
     if (first && lane < rs.want) rk[lane] = 0ull;
     wave_sync();                                         // every read of the histogram is done
@@ -1453,9 +1453,11 @@ __device__ __attribute__((always_inline)) inline int process_beam_wave(
         runs_finish(rs, f, p, beam, hist, floor_b, lane, rk, rb);
         return fx | (int)slot;
     }
-    if (lane == 0) am[0] = word;
-    wave_sync();
-    detect_echoes(f, p, beam, hist, am, floor_b, lane);
+    if constexpr (RANK) {
+        if (lane == 0) am[0] = word;
+        wave_sync();
+        detect_echoes(f, p, beam, hist, am, floor_b, lane);
+    }
     return fx | (int)slot;
 }
 
@@ -1745,8 +1747,12 @@ void k_footprint_batch_wave(BatchArgs a)
 // for each of these steps and three of them idle in most.  Frames with
 // 2048 bins, times with the pre-pass (about 20 us): 8000 beams of 100 samples
 // 76 us in groups, 49 us here; 32000 beams 225 us and 104 us.
+// Instances with sun or kept waveforms do not fit 64 registers: one pass runs
+// at six waves per SIMD instead of eight with 4 to 16 registers in memory
+// (66 frames each: 0.89 of the time with sun, 0.99 with waveforms, 0.94 with
+// both), four passes stay at four (three: 1.10 to 1.12 of the time).
 template <int NP, bool SUN, bool KEEP>
-__global__ __launch_bounds__(kFootprintThreads) __attribute__((amdgpu_waves_per_eu(NP == 1 ? 8 : 4)))
+__global__ __launch_bounds__(kFootprintThreads) __attribute__((amdgpu_waves_per_eu(NP == 1 ? (SUN || KEEP ? 6 : 8) : 4)))
 void k_footprint_wave(FootprintArgs a)
 {
     constexpr int G = kWaves;
@@ -1754,7 +1760,6 @@ void k_footprint_wave(FootprintArgs a)
     const int RS = conv_stride(a.p.R, a.p.J);
     float* taps = (float*)lds4 + G * RS;
     __shared__ unsigned nzw[kWaves];
-    __shared__ unsigned amask[kWaves][kMaxBins / kPassBins + 1];
     __shared__ unsigned long long rkey[kWaves][kMaxEchoes];   // first runs: peak keys, bins
     __shared__ int2 rbin[kWaves][kMaxEchoes];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1778,8 +1783,8 @@ void k_footprint_wave(FootprintArgs a)
             clear_passes<NP>(hist, a.p.R, (unsigned)left >> 8 & 0xffu, (unsigned)left >> 16 & 0xffu, lane);
             if (lane == 0) nzw[wave] = 0u;
             wave_sync();
-            left = process_beam_wave<NP, SUN, KEEP, false>(a.f, a.p, beam, hist, RS, taps, &nzw[wave],
-                                                           amask[wave], lane, rkey[wave], rbin[wave]);
+            left = process_beam_wave<NP, SUN, KEEP, false, false>(a.f, a.p, beam, hist, RS, taps, &nzw[wave], nullptr,
+                                                                  lane, rkey[wave], rbin[wave]);
             wave_sync();                                 // the slot is reused
         }
     }
@@ -1887,7 +1892,9 @@ hipError_t launch_footprint(hipStream_t s, const FootprintArgs& a)
 
 hipError_t launch_footprint_wave(hipStream_t s, const FootprintArgs& a)
 {
-    if (a.G != kWaves || a.p.R > kWaveMaxBins) return hipErrorInvalidValue;
+    if (a.G != kWaves || a.p.R > kWaveMaxBins || a.p.select == LIDAR_ECHO_STRONGEST ||
+        a.p.select == LIDAR_ECHO_LONGEST)
+        return hipErrorInvalidValue;
     return a.p.R <= kWavePassBins ? launch_wave_p<1>(s, a) : launch_wave_p<kWavePasses>(s, a);
 }
 

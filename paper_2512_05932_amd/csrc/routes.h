@@ -34,8 +34,13 @@ inline bool one_device(int memory, int handle, int current)
 // Measured over 2304 frames (2048 to 32000 beams in grids, rows and Lissajous
 // figures; 512, 1200 and 2048 bins; i.i.d. surfaces, a road and a flat wall on
 // 1024 x 512 and 4096 x 1024 pixels).  The frames that the rule sends to the
-// waves take 0.64 of the time on average and 1.01 of it at most.  Left to
-// the groups, with their times (groups, waves):
+// waves take 0.64 of the time on average and 1.01 of it at most.  With sun or
+// kept waveforms, whose instances hold more registers, and with up to 120000
+// beams: 610 frames 0.46 to 0.69 on average (plain gains least), 0.90 at most with
+// up to 32000 beams; beyond, only groups of three and four lose, by up to 1.07
+// with 513 to 1600 bins and up to 1.14 on i.i.d. surfaces with 2048 (on the
+// road and the wall those take 0.62 to 0.89).  Left to the groups, with their
+// times (groups, waves):
 //  * few groups: 2048 single beams of a 9 x 7 kernel 24.6 and 36.9 us;
 //  * full groups, whose pixels the workgroup reads once: 24000 beams of a 9 x 7
 //    kernel in 6000 groups (2048 bins) 1.09 of the time;
