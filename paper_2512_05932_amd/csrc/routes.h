@@ -27,25 +27,28 @@ inline bool one_device(int memory, int handle, int current)
 
 // Whether a single frame whose groups hold up to four beams runs with a wave per
 // group (which takes the group's beams one after another) instead of a
-// workgroup per group.  A beam takes the wave longer, so there have to be
-// several times as many groups as workgroups resident on the chip: `held` per
-// CU of the group kernel (by its LDS), `held_wave` per CU of the wave kernel.
+// workgroup per group.  A beam takes the wave longer, and the frame as long as
+// its fullest groups, so there have to be enough groups to fill the chip: the
+// more, the more beams share a group (their pixels are read once for all there)
+// and the more groups a CU holds.  `held` per CU of the group kernel (by its
+// LDS), `held_wave` per CU of the wave kernel (eight with one pass).
 //
-// Measured over 2304 frames (2048 to 32000 beams in grids, rows and Lissajous
-// figures; 512, 1200 and 2048 bins; i.i.d. surfaces, a road and a flat wall on
-// 1024 x 512 and 4096 x 1024 pixels).  The frames that the rule sends to the
-// waves take 0.64 of the time on average and 1.01 of it at most.  With sun or
-// kept waveforms, whose instances hold more registers, and with up to 120000
-// beams: 610 frames 0.46 to 0.69 on average (plain gains least), 0.90 at most with
-// up to 32000 beams; beyond, only groups of three and four lose, by up to 1.07
-// with 513 to 1600 bins and up to 1.14 on i.i.d. surfaces with 2048 (on the
-// road and the wall those take 0.62 to 0.89).  Left to the groups, with their
-// times (groups, waves):
-//  * few groups: 2048 single beams of a 9 x 7 kernel 24.6 and 36.9 us;
-//  * full groups, whose pixels the workgroup reads once: 24000 beams of a 9 x 7
-//    kernel in 6000 groups (2048 bins) 1.09 of the time;
+// The lines lie where the last frames that lose end, over 289 frames of 1200 to
+// 20000 beams in grids, Lissajous figures and jittered grids on a road and on
+// i.i.d. surfaces (512, 1200 and 2048 bins) and 2520 frames of 1200 to 60000
+// beams in runs of one, two and four, on these and on a flat wall, with and
+// without sun, kept waveforms and raw selection.  Against the groups the first
+// take 0.91 of the time on average (0.99 with every frame of 2048 beams in waves,
+// 2.2 at most there) and 1.04 at most, the second 0.80 and
+// 1.17 at most (40000 beams in groups of four on i.i.d. surfaces, 2048 bins, which
+// on the road take 0.62 to 0.89).  With their times (groups, waves):
+//  * single beams: 2432 of an 11 x 11 kernel 33.1 and 25.7 us;
+//  * few groups: 2048 beams of a 9 x 7 kernel in 1978 groups 24.6 and 36.9 us;
+//  * full groups: 24000 beams of a 9 x 7 kernel in 6000 groups (2048 bins) 1.09 of
+//    the time; raw selections, whose waveforms are not convolved, 0.74 to 1.40
+//    with 7000 full groups;
 //  * 513 to some 1600 bins, where a CU holds more groups: 6504 beams of a 9 x 7
-//    kernel, 1200 bins, 40.9 and 47.9 us;
+//    kernel in 5636 groups, 1200 bins, 40.9 and 47.9 us;
 //  * long kernels, whose rows or columns the wave walks alone: 4000 beams of a
 //    1 x 141 kernel 38.5 and 51.1 us; kernels of more than 160 cells: 4000 beams
 //    of 400 samples 36 and 46 us;
@@ -70,8 +73,14 @@ inline bool frame_in_waves(const FrameShape& f)
     const int extent = f.kernel_w > f.kernel_h ? f.kernel_w : f.kernel_h;
     if ((long)f.kernel_w * f.kernel_h > kNarrowCells || extent > kLong) return false;
     const double per_group = (double)f.beams / (double)f.groups;
-    double need = 3500.0 + 1000.0 * per_group + (extent > kRound ? 2000.0 : 0.0);
-    if (f.held > f.held_wave) need = need * f.held / f.held_wave;
+    if (f.select >= LIDAR_ECHO_RAW_STRONGEST && per_group > 2.5) return false;
+    double need = 2000.0;                                            // single beams
+    if (per_group > 1.01) {
+        if (f.held_wave >= 8) need = 3450.0 + 330.0 * per_group;
+        else if (f.held > f.held_wave) need = 5000.0 + 900.0 * per_group;
+        else need = 3500.0 + 1000.0 * per_group;
+        if (extent > kRound) need += 2000.0;
+    }
     return (double)f.groups >= need;
 }
 

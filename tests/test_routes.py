@@ -30,7 +30,16 @@ def test_a_kernel_writes_only_memory_of_the_one_device():
     ((5000, 4688, 11, 11, 0, 0, 4, 4), True),         # a stateless frame
     ((9000, 9000, 13, 12, 2, 0, 8, 8), True),
     ((9000, 9000, 13, 12, 5, 0, 8, 8), True),
+    ((2432, 2432, 11, 11, 0, 0, 8, 8), True),         # single beams
+    ((3000, 3000, 9, 9, 0, 0, 7, 4), True),
+    ((4129, 4129, 41, 3, 4, 0, 4, 4), True),
+    ((8196, 4320, 7, 7, 0, 0, 8, 8), True),           # pairs
+    ((13500, 7400, 9, 9, 0, 0, 7, 4), True),
+    ((19500, 4920, 11, 11, 0, 0, 8, 8), True),        # full groups
     # each of these was slower by the wave (1.06 to 2.6 times)
+    ((1256, 1256, 9, 9, 4, 0, 8, 8), False),
+    ((3900, 3250, 5, 5, 0, 0, 7, 4), False),
+    ((26000, 6624, 9, 9, 4, 0, 8, 8), False),         # full groups, raw selection
     ((2048, 1978, 9, 7, 0, 0, 8, 8), False),          # few groups
     ((4000, 3478, 9, 7, 0, 0, 8, 8), False),
     ((4000, 1000, 9, 7, 0, 0, 8, 8), False),          # full groups
