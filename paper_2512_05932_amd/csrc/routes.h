@@ -90,17 +90,21 @@ inline bool frame_in_waves(const FrameShape& f)
 // left.  Times in us with 1, 2, 4 and 8 bands: 28800 beams of 83000 samples 932,
 // 831, 756, 772; 14400 beams of 21000 corrected samples, which read less for their
 // FP64 arithmetic, 888, 796, 779, 750 (another scene 1010, 796, 727, 729); 32000
-// beams of 105 samples (in waves) 141, 140, 135, 133.  Frames of few groups are
-// on the chip at once and only lose: 7001 beams of 729 samples in 3330 groups
-// 47.0, 48.8, 50.0, 49.6.  Over 378 frames of 289 to 9801 cells, 1 to 20000 beams,
-// four bands from 4000 groups on take 0.985 of the time with one band (1.03 at
-// most, surfaces of even cost; 0.76 at least, a road under a sky); eight bands in
-// every frame took up to 1.10.  Frames of narrow kernels gain from 8000 groups
-// on: 0.965 to 0.98, where fewer groups take up to 1.10.
+// beams of 105 samples (in waves) 137, 136, 133, 131.  Over 300 frames of 25 to
+// 100000 cells and 200 to 20000 beams on a road and on i.i.d. surfaces:
+//  * corrected ranges: 8 bands take 0.90 of the time with one from 1000 groups on
+//    (0.82 to 1.00), 0.98 with 600 to 1000, and 4 bands 0.91;
+//  * more than 1000 cells: 4 bands take 0.95 from 1000 groups on (0.81 to 1.08),
+//    1.00 with fewer (0.93 to 1.10);
+//  * 161 to 1000 cells: 4 bands take 0.97 from 1500 groups on (0.89 to 1.02),
+//    1.00 with 1000 to 1500 (0.92 to 1.10);
+//  * up to 160 cells: within 0.02 of each other, except for large frames on a
+//    road, above.
 inline int xcd_bands(long groups, long cells, bool corrected)
 {
-    if (groups < (cells > kNarrowCells ? 4000 : 8000)) return 1;
-    return corrected ? 8 : 4;
+    if (corrected) return groups < 600 ? 1 : 8;
+    if (cells <= kNarrowCells) return groups < 8000 ? 1 : 8;
+    return groups < (cells > 1000 ? 1000 : 1500) ? 1 : 4;
 }
 
 // Groups of a band, and of an XCD's bands together (its last ones may lie past

@@ -59,13 +59,14 @@ def test_frames_in_waves(frame, waves):
     assert routes.in_waves(*frame) == waves
 
 
-@pytest.mark.parametrize("corrected", [False, True])
-@pytest.mark.parametrize("cells,line", [(121, 8000), (160, 8000), (161, 4000), (144225, 4000)])
-def test_bands_of_groups(cells, line, corrected):
-    """Every group goes to one XCD once; one band per XCD below the line, four (corrected ranges: eight) from it on."""
-    for n in [*range(1, 70), 3330, 3999, 4000, 4001, 7199, 7999, 8000, 8031, 8032, 28800]:
+@pytest.mark.parametrize("cells,corrected,line,many", [
+    (121, False, 8000, 8), (160, False, 8000, 8), (161, False, 1500, 4), (1000, False, 1500, 4), (1001, False, 1000, 4),
+    (144225, False, 1000, 4), (25, True, 600, 8), (144225, True, 600, 8)])
+def test_bands_of_groups(cells, corrected, line, many):
+    """Every group goes to one XCD once; one band per XCD below the line, several from it on."""
+    for n in [*range(1, 70), 599, 600, 999, 1000, 1001, 1499, 1500, 3330, 7199, 7999, 8000, 8031, 8032, 28800]:
         band, chunk = routes.xcd_share(n, cells, corrected)
-        bands = 1 if n < line else 8 if corrected else 4
+        bands = 1 if n < line else many
         assert band == -(-n // (8 * bands)) and chunk % band == 0 and chunk // band <= bands
         seen = sorted(g for x in range(8) for i in range(chunk) if (g := (i // band * 8 + x) * band + i % band) < n)
         assert seen == list(range(n)), n
