@@ -95,7 +95,7 @@ inline bool frame_in_waves(const FrameShape& f)
 //  * corrected ranges: 8 bands take 0.90 of the time with one from 1000 groups on
 //    (0.82 to 1.00), 0.98 with 600 to 1000, and 4 bands 0.91;
 //  * more than 1000 cells: 4 bands take 0.95 from 1000 groups on (0.81 to 1.08),
-//    1.00 with fewer (0.93 to 1.10);
+//    0.99 with 400 to 1000 (0.93 to 1.05), 1.00 with fewer;
 //  * 161 to 1000 cells: 4 bands take 0.97 from 1500 groups on (0.89 to 1.02),
 //    1.00 with 1000 to 1500 (0.92 to 1.10);
 //  * up to 160 cells: within 0.02 of each other, except for large frames on a
@@ -104,7 +104,7 @@ inline int xcd_bands(long groups, long cells, bool corrected)
 {
     if (corrected) return groups < 600 ? 1 : 8;
     if (cells <= kNarrowCells) return groups < 8000 ? 1 : 8;
-    return groups < (cells > 1000 ? 1000 : 1500) ? 1 : 4;
+    return groups < (cells > 1000 ? 400 : 1500) ? 1 : 4;
 }
 
 // Groups of a band, and of an XCD's bands together (its last ones may lie past
