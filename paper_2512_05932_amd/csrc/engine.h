@@ -591,7 +591,7 @@ struct SurNet {
     bool ready = false;
     bool det = false;                   // LIDAR_DETERMINISTIC: gradients in a fixed order
 };
-struct SurWork {                        // activations of up to `cap` rows
+struct SurWork {                        // activations of up to `cap` rows (training)
     long cap = 0;
     DevBuf<float> Z1, Z2, Z3, Y, dH, loss;
     DevBuf<uint16_t> H1, H2, H3, dYb, dZ1, dZ2, dZ3;

@@ -2133,7 +2133,7 @@ static lidar_status simulate_surrogate(lidar_sim* h)
     HIP_TRY(h, h->d_counts.ensure(B), "allocate counts");
     if (keep) HIP_TRY(h, h->d_waves.ensure((size_t)B * R), "allocate waveforms");
     HIP_TRY(h, h->s_X.ensure((size_t)B * kSurIn), "allocate surrogate inputs");
-    HIP_TRY(h, h->work.ensure(B), "allocate surrogate workspace");
+    HIP_TRY(h, h->work.Y.ensure((size_t)B * kSurOut), "allocate surrogate outputs");
     HIP_TRY(h, h->s_groups_fb.ensure((size_t)fs.n_groups * h->G), "allocate fallback groups");
     HIP_TRY(h, h->s_items.ensure(fs.n_groups), "allocate fallback items");
     if (!h->s_cnt.p) {
@@ -2371,13 +2371,6 @@ static lidar_status sur_check(lidar_sim* h, const void* x, const void* y, uint32
 {
     if (!x || !y || n == 0) return fail(h, LIDAR_E_INVALID, "surrogate call needs x, outputs and n >= 1");
     if (!h->net.ready) return fail(h, LIDAR_E_STATE, "no surrogate weights set");
-    HIP_TRY(h, h->work.ensure((long)n), "allocate surrogate workspace");
-    if (!h->work.blas_tried && !h->net.det) {
-        // the library GEMMs of the training products (the own kernel runs
-        // where the library cannot start)
-        h->work.blas = blas_create();
-        h->work.blas_tried = true;
-    }
     return LIDAR_OK;
 }
 
@@ -2397,6 +2390,13 @@ lidar_status lidar_sim_surrogate_forward(lidar_sim* h, const void* x, float* y, 
 static lidar_status sur_grads(lidar_sim* h, const void* x, const float* labels, uint32_t n, float* grads, float* loss)
 {
     LIDAR_TRY(sur_check(h, x, labels, n));
+    HIP_TRY(h, h->work.ensure((long)n), "allocate surrogate workspace");
+    if (!h->work.blas_tried && !h->net.det) {
+        // the library GEMMs of the training products (the own kernel runs
+        // where the library cannot start)
+        h->work.blas = blas_create();
+        h->work.blas_tried = true;
+    }
     constexpr size_t kGradBytes = (size_t)kSurParams * sizeof(float);
     auto own = [&](float* p, size_t bytes, const float* other, size_t other_bytes, float* ours) {
         const bool direct = p && (uintptr_t)p % sizeof(float) == 0 &&
