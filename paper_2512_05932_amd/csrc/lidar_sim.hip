@@ -2378,7 +2378,16 @@ lidar_status lidar_sim_surrogate_forward(lidar_sim* h, const void* x, float* y, 
 {
     if (!h) return LIDAR_E_INVALID;
     LIDAR_TRY(sur_check(h, x, y, n));
-    HIP_TRY(h, sur_infer(h->stream, h->net, (const uint16_t*)x, (long)n, y), "surrogate forward");
+    // workgroups write their rows' outputs while others read their inputs:
+    // outputs that share memory with the inputs are copied
+    const size_t bytes = (size_t)n * kSurOut * sizeof(float);
+    float* out = y;
+    if (ranges_overlap(x, (size_t)n * kSurIn * sizeof(uint16_t), y, bytes)) {
+        HIP_TRY(h, h->work.Y.ensure((size_t)n * kSurOut), "allocate surrogate outputs");
+        out = h->work.Y.p;
+    }
+    HIP_TRY(h, sur_infer(h->stream, h->net, (const uint16_t*)x, (long)n, out), "surrogate forward");
+    if (out != y) HIP_TRY(h, hipMemcpyAsync(y, out, bytes, hipMemcpyDeviceToDevice, h->stream), "copy outputs");
     return LIDAR_OK;
 }
 

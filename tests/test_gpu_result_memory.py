@@ -123,3 +123,24 @@ def test_overlapping_destinations_are_written_in_order(lidar, batch):
             np.testing.assert_array_equal(room.cpu().numpy(), ref)
     finally:
         sim.close()
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 100, 128, 129, 60000])
+@pytest.mark.parametrize("end", [False, True])
+def test_forward_outputs_inside_the_rows(lidar, n, end):
+    """The first rows' memory, or the last's (60000 rows: those are read long after the first outputs are there)."""
+    import torch
+    sim, bits, _ = _net(lidar, min(n, 700), False)
+    try:
+        x = torch.from_numpy(bits.copy()).cuda()[torch.arange(n, device="cuda") % len(bits)].contiguous()
+        y = torch.empty((n, 16), device="cuda")
+        sim.surrogate_forward(x, y)
+        rows = torch.empty_like(x)
+        for _ in range(5):
+            rows.copy_(x)
+            at = (528 - 16) * n if end else 0
+            inside = rows.view(torch.float32).view(-1)[at:at + 16 * n].view(n, 16)
+            sim.surrogate_forward(rows, inside)
+            assert torch.equal(inside, y)
+    finally:
+        sim.close()
