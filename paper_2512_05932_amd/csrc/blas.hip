@@ -3,9 +3,9 @@
 //
 // A GemmArgs product C[M][N] (row-major, ldc) = sum_k A(i, k) B(k, j) is the
 // column-major product D (N x M, ld ldc) = X (N x K) Y (K x M) with
-// X(j, k) = B(k, j) and Y(k, i) = A(i, k); a unit stride along k or along the
-// other index of an operand gives its stored column-major matrix and whether
-// it enters transposed.  Descriptors and the heuristic's algorithm are cached
+// X(j, k) = B(k, j) and Y(k, i) = A(i, k); B's unit stride, along k or along j,
+// gives its stored column-major matrix and whether it enters transposed, A is
+// stored as Y.  Descriptors and the heuristic's algorithm are cached
 // per shape; the workspace is the context's.
 #include <hipblaslt/hipblaslt.h>
 
@@ -25,7 +25,7 @@ struct Plan {
     size_t ws = 0;
 };
 
-using Key = std::tuple<int, int, int, int, int, long, long, long>;
+using Key = std::tuple<int, int, int, int, long, long, long>;
 
 }  // namespace
 
@@ -65,9 +65,9 @@ void blas_destroy(BlasCtx* c)
 hipError_t blas_gemm(BlasCtx* c, hipStream_t s, const GemmArgs& g)
 {
     if (!c || g.M <= 0 || g.N <= 0) return g.M <= 0 || g.N <= 0 ? hipSuccess : hipErrorNotSupported;
-    // X (N x K): from B; Y (K x M): from A
-    hipblasOperation_t opx, opy;
-    long ldx, ldy;
+    // X (N x K): from B
+    hipblasOperation_t opx;
+    long ldx;
     if (g.sbn == 1) {
         opx = HIPBLAS_OP_N;                       // stored N x K, column k at k * sbk
         ldx = g.sbk;
@@ -77,30 +77,20 @@ hipError_t blas_gemm(BlasCtx* c, hipStream_t s, const GemmArgs& g)
     } else {
         return hipErrorNotSupported;
     }
-    if (g.sak == 1) {
-        opy = HIPBLAS_OP_N;                       // stored K x M, column i at i * sam
-        ldy = g.sam;
-    } else if (g.sam == 1) {
-        opy = HIPBLAS_OP_T;                       // stored M x K, column k at k * sak
-        ldy = g.sak;
-    } else {
-        return hipErrorNotSupported;
-    }
-    const Key key{g.M, g.N, g.K, (int)opx, (int)opy, ldx, ldy, g.ldc};
+    const Key key{g.M, g.N, g.K, (int)opx, ldx, g.lda, g.ldc};
     auto it = c->plans.find(key);
     if (it == c->plans.end()) {
         Plan p;
         bool ok = hipblasLtMatmulDescCreate(&p.desc, HIPBLAS_COMPUTE_32F, HIP_R_32F) == HIPBLAS_STATUS_SUCCESS;
-        const int32_t ta = opx, tb = opy;
+        const int32_t ta = opx, tb = HIPBLAS_OP_N;
         ok = ok && hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof(ta)) ==
                        HIPBLAS_STATUS_SUCCESS;
         ok = ok && hipblasLtMatmulDescSetAttribute(p.desc, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof(tb)) ==
                        HIPBLAS_STATUS_SUCCESS;
-        // stored shapes: X is N x K (or K x N), Y is K x M (or M x K), D is N x M
+        // stored shapes: X is N x K (or K x N), Y is K x M, D is N x M
         ok = ok && hipblasLtMatrixLayoutCreate(&p.a, HIP_R_16BF, opx == HIPBLAS_OP_N ? g.N : g.K,
                                                opx == HIPBLAS_OP_N ? g.K : g.N, ldx) == HIPBLAS_STATUS_SUCCESS;
-        ok = ok && hipblasLtMatrixLayoutCreate(&p.b, HIP_R_16BF, opy == HIPBLAS_OP_N ? g.K : g.M,
-                                               opy == HIPBLAS_OP_N ? g.M : g.K, ldy) == HIPBLAS_STATUS_SUCCESS;
+        ok = ok && hipblasLtMatrixLayoutCreate(&p.b, HIP_R_16BF, g.K, g.M, g.lda) == HIPBLAS_STATUS_SUCCESS;
         ok = ok && hipblasLtMatrixLayoutCreate(&p.d, HIP_R_32F, g.N, g.M, g.ldc) == HIPBLAS_STATUS_SUCCESS;
         hipblasLtMatmulPreference_t pref = nullptr;
         ok = ok && hipblasLtMatmulPreferenceCreate(&pref) == HIPBLAS_STATUS_SUCCESS;

@@ -419,10 +419,10 @@ __host__ __device__ inline bool sur_is_weight(long i)
 }
 
 // C[M][N] (FP32, row stride ldc) = sum_k A(i, k) B(k, j), BF16 operands with
-// A(i, k) = A[i sam + k sak] and B(k, j) = B[k sbk + j sbn].
+// A(i, k) = A[i lda + k] and B(k, j) = B[k sbk + j sbn].
 struct GemmArgs {
     const uint16_t* A;
-    long sam, sak;
+    long lda;
     const uint16_t* B;
     long sbk, sbn;
     float* C;

@@ -48,7 +48,6 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // load mapping: consecutive threads walk the operand's unit-stride axis
-    const bool a_kfast = g.sak == 1;
     const bool b_kfast = g.sbk == 1;
     // this workgroup's share of K (whole tiles)
     const int kchunk = ((g.K + g.ksplit - 1) / g.ksplit + kTileK - 1) / kTileK * kTileK;
@@ -57,10 +56,9 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g)
 #pragma unroll
         for (int q = 0; q < (kTileM * kTileK) / 256; ++q) {
             const int e = tid + 256 * q;
-            const int r = a_kfast ? e / kTileK : e % kTileM;
-            const int k = a_kfast ? e % kTileK : e / kTileM;
+            const int r = e / kTileK, k = e % kTileK;
             const int gi = m0 + r, gk = k0 + k;
-            As[r][k] = (gi < g.M && gk < kend) ? g.A[(long)gi * g.sam + (long)gk * g.sak] : (uint16_t)0;
+            As[r][k] = (gi < g.M && gk < kend) ? g.A[(long)gi * g.lda + gk] : (uint16_t)0;
         }
 #pragma unroll
         for (int q = 0; q < (kTileN * kTileK) / 256; ++q) {
@@ -632,8 +630,9 @@ hipError_t launch_gemm_bf16(hipStream_t s, const GemmArgs& g0, bool det)
     if (g0.M <= 0 || g0.N <= 0) return hipSuccess;
     GemmArgs g = g0;
     const long tiles = (long)((g.N + kTileN - 1) / kTileN) * ((g.M + kTileM - 1) / kTileM);
-    // few output tiles and a long K (weight gradients): split K over the grid
-    // (not when deterministic: the atomic adds of the parts come in any order)
+    // few output tiles and a long K (the first layer on few rows): split K over
+    // the grid (not when deterministic: the atomic adds of the parts come in any
+    // order)
     g.ksplit = 1;
     while (!det && tiles * g.ksplit < 512 && g.K / (g.ksplit * 2) >= 4 * kTileK) g.ksplit *= 2;
     if (g.ksplit > 1) {
@@ -772,11 +771,11 @@ static hipError_t gemm(hipStream_t s, const GemmArgs& g, bool det, BlasCtx* blas
     return launch_gemm_bf16(s, g, det);
 }
 
-// Z = A W (+ bias, GELU) with A [n][k] row-major BF16 and W [k][c] BF16
+// Z = A W (before the bias) with A [n][k] row-major BF16 and W [k][c] BF16
 static hipError_t dense(hipStream_t s, const uint16_t* A, int k, const uint16_t* W, int c, long n,
                         float* Z, bool det, BlasCtx* blas)
 {
-    GemmArgs g{A, k, 1, W, c, 1, Z, c, (int)n, c, k, 1};
+    GemmArgs g{A, k, W, c, 1, Z, c, (int)n, c, k, 1};
     return gemm(s, g, det, blas);
 }
 
@@ -822,7 +821,7 @@ hipError_t sur_infer(hipStream_t s, SurNet& net, const uint16_t* X, long n, floa
 static hipError_t input_grad(hipStream_t s, const uint16_t* D, int out, const uint16_t* W, int in,
                              long n, float* dH, bool det, BlasCtx* blas)
 {
-    GemmArgs g{D, out, 1, W, 1, out, dH, in, (int)n, in, out, 1};
+    GemmArgs g{D, out, W, 1, out, dH, in, (int)n, in, out, 1};
     return gemm(s, g, det, blas);
 }
 

@@ -30,7 +30,6 @@ constexpr int kThreads = 256;
 constexpr int kTileWaves = 8, kTileThreads = 64 * kTileWaves;
 constexpr int kDense = 8;                     // window columns correlated together
 constexpr int kMaxHalf = kRsMaxHalf;          // M, N <= 127
-constexpr int kMaxWords = (kMaxBins + 31) / 32;
 // 64-row groups of a tile's window rows, 64-column groups of its window columns
 constexpr int kRowGroups = (kRows + 2 * kMaxHalf + 63) / 64;
 constexpr int kMaxColGroups = (kCols + 2 * kMaxHalf + 63) / 64;
