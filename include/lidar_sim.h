@@ -212,7 +212,9 @@ typedef struct {
     uint64_t n_beams;          /* sum over frames */
     uint64_t n_items;          /* (frame, beam group) work items */
     uint64_t samples;          /* sum over frames of beam-pixel samples */
-    uint32_t grid;             /* workgroups of the persistent launch */
+    uint32_t grid;             /* workgroups of the persistent launch: the group
+                                  schedule's, or the wave schedule's where every
+                                  frame runs in that */
     uint32_t graph;            /* 1 when the batch replays a captured HIP graph */
     uint32_t autotuned;        /* 1 when the tiles came from timed trials */
     uint32_t wave_items;       /* items of frames on the wave schedule (one wave per

@@ -88,14 +88,15 @@ inline bool frame_in_waves(const FrameShape& f)
 // column order, so one band per XCD keeps the most pixels in its L2, but columns
 // differ in cost, and workgroups go to the XCDs in turn, whatever these have
 // left.  Times in us with 1, 2, 4 and 8 bands: 28800 beams of 83000 samples 932,
-// 831, 756, 772; 14400 beams of 21000 corrected samples, which read less for their
-// FP64 arithmetic, 888, 796, 779, 750 (another scene 1010, 796, 727, 729); 32000
-// beams of 105 samples (in waves) 137, 136, 133, 131.  Over 300 frames of 25 to
-// 100000 cells and 200 to 20000 beams on a road and on i.i.d. surfaces:
+// 831, 756, 772 (the mean of six scenes 760 and 765 with 4 and 8, but 833 and 824
+// on the benchmark's); 14400 beams of 21000 corrected samples, which read less for
+// their FP64 arithmetic, 888, 796, 779, 750 (another scene 1010, 796, 727, 729);
+// 32000 beams of 105 samples (in waves) 137, 136, 133, 131.  Over 300 frames of 25
+// to 100000 cells and 200 to 20000 beams on a road and on i.i.d. surfaces:
 //  * corrected ranges: 8 bands take 0.90 of the time with one from 1000 groups on
 //    (0.82 to 1.00), 0.98 with 600 to 1000, and 4 bands 0.91;
-//  * more than 1000 cells: 4 bands take 0.95 from 1000 groups on (0.81 to 1.08),
-//    0.99 with 400 to 1000 (0.93 to 1.05), 1.00 with fewer;
+//  * more than 1000 cells: 8 bands take 0.95 from 1000 groups on (0.75 to 1.10), as 4
+//    do; with 400 to 1000 groups 4 take 0.99 (0.93 to 1.05) and 8 take 1.01;
 //  * 161 to 1000 cells: 4 bands take 0.97 from 1500 groups on (0.89 to 1.02),
 //    1.00 with 1000 to 1500 (0.92 to 1.10);
 //  * up to 160 cells: within 0.02 of each other, except for large frames on a
@@ -104,7 +105,8 @@ inline int xcd_bands(long groups, long cells, bool corrected)
 {
     if (corrected) return groups < 600 ? 1 : 8;
     if (cells <= kNarrowCells) return groups < 8000 ? 1 : 8;
-    return groups < (cells > 1000 ? 400 : 1500) ? 1 : 4;
+    if (cells <= 1000) return groups < 1500 ? 1 : 4;
+    return groups < 400 ? 1 : groups < 1000 ? 4 : 8;
 }
 
 // Groups of a band, and of an XCD's bands together (its last ones may lie past

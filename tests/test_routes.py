@@ -59,14 +59,14 @@ def test_frames_in_waves(frame, waves):
     assert routes.in_waves(*frame) == waves
 
 
-@pytest.mark.parametrize("cells,corrected,line,many", [
-    (121, False, 8000, 8), (160, False, 8000, 8), (161, False, 1500, 4), (1000, False, 1500, 4), (1001, False, 400, 4),
-    (144225, False, 400, 4), (25, True, 600, 8), (144225, True, 600, 8)])
-def test_bands_of_groups(cells, corrected, line, many):
-    """Every group goes to one XCD once; one band per XCD below the line, several from it on."""
-    for n in [*range(1, 70), 399, 400, 401, 599, 600, 999, 1000, 1001, 1499, 1500, 3330, 7199, 7999, 8000, 8031, 8032, 28800]:
+@pytest.mark.parametrize("cells,corrected,lines", [
+    (121, False, {8000: 8}), (160, False, {8000: 8}), (161, False, {1500: 4}), (1000, False, {1500: 4}),
+    (1001, False, {400: 4, 1000: 8}), (144225, False, {400: 4, 1000: 8}), (25, True, {600: 8}), (144225, True, {600: 8})])
+def test_bands_of_groups(cells, corrected, lines):
+    """Every group goes to one XCD once; one band per XCD below the lines, several from them on."""
+    for n in [*range(1, 70), 399, 400, 401, 599, 600, 999, 1000, 1001, 1499, 1500, 3330, 7199, 7999, 8000, 8031, 28800]:
         band, chunk = routes.xcd_share(n, cells, corrected)
-        bands = 1 if n < line else many
+        bands = max([1, *(b for line, b in lines.items() if n >= line)])
         assert band == -(-n // (8 * bands)) and chunk % band == 0 and chunk // band <= bands
         seen = sorted(g for x in range(8) for i in range(chunk) if (g := (i // band * 8 + x) * band + i % band) < n)
         assert seen == list(range(n)), n
