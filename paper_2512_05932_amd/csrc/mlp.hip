@@ -228,7 +228,7 @@ void k_gelu_back(const float4* dH, const float4* Z, const float4* bias, bf16x4* 
 // pieces into a [column][row] tile in LDS, from where a fragment is one
 // 16-byte read; the next step's rows are loaded meanwhile.
 // A library product per layer with 16 to 68 workgroups, and the column sums
-// apart, took 28 us and 16 us each (4096 rows); all four layers here 19 us,
+// apart, took 28 us and 16 us each (4096 rows); all four layers here 29 us,
 // bound by the latency of the loads (without the atomics it takes as long).
 constexpr int kGradT = 64;                   // tile of dW: in x out
 constexpr int kGradK = 64;                   // rows per step
