@@ -39,9 +39,11 @@ inline bool one_device(int memory, int handle, int current)
 // beams in runs of one, two and four, on these and on a flat wall, with and
 // without sun, kept waveforms and raw selection.  Against the groups the first
 // take 0.91 of the time on average (0.99 with every frame of 2048 beams in waves,
-// 2.2 at most there) and 1.04 at most, the second 0.80 and
-// 1.17 at most (40000 beams in groups of four on i.i.d. surfaces, 2048 bins, which
-// on the road take 0.62 to 0.89).  With their times (groups, waves):
+// 2.2 at most there) and 1.04 at most, the second 0.80 and 1.17 at most.  What
+// loses is shared groups on i.i.d. surfaces with 2048 bins, where every pixel ends a
+// run: at random places 0.92 to 1.35 (kept waveforms), where the road takes 0.62 to
+// 0.90 and the wall 0.59 to 0.83.  Left to the groups, with their times (groups,
+// waves):
 //  * single beams: 2432 of an 11 x 11 kernel 33.1 and 25.7 us;
 //  * few groups: 2048 beams of a 9 x 7 kernel in 1978 groups 24.6 and 36.9 us;
 //  * full groups: 24000 beams of a 9 x 7 kernel in 6000 groups (2048 bins) 1.09 of
@@ -52,8 +54,11 @@ inline bool one_device(int memory, int handle, int current)
 //  * long kernels, whose rows or columns the wave walks alone: 4000 beams of a
 //    1 x 141 kernel 38.5 and 51.1 us; kernels of more than 160 cells: 4000 beams
 //    of 400 samples 36 and 46 us;
-//  * range intervals, a step per bin of a pixel's range: 8000 beams of an 11 x 11
-//    kernel 93 and 240 us (2048 bins);
+//  * range intervals with more than 512 bins, a step per bin of a pixel's range: 8000
+//    beams of an 11 x 11 kernel 93 and 240 us (2048 bins).  With one pass they are
+//    as centre ranges, whatever the bins' width (2268 frames): single beams gain
+//    from 2500 groups on (0.31 to 0.87 of the time from 3300 on), beams that share
+//    groups from 6500 on (0.41 to 1.12), full groups lose up to 1.7;
 //  * selections that need every run's key, which are not found as the waveform
 //    is written: 17256 beams of 64 samples, strongest echo, 92 and 98 us.
 struct FrameShape {
@@ -69,14 +74,18 @@ inline bool frame_in_waves(const FrameShape& f)
 {
     constexpr int kRound = 13, kLong = 41;
     if (f.select == LIDAR_ECHO_STRONGEST || f.select == LIDAR_ECHO_LONGEST) return false;
-    if (f.range_mode != LIDAR_RANGE_CENTRE || f.groups <= 0) return false;
+    if ((f.range_mode != LIDAR_RANGE_CENTRE && f.range_mode != LIDAR_RANGE_INTERVAL) || f.groups <= 0) return false;
     const int extent = f.kernel_w > f.kernel_h ? f.kernel_w : f.kernel_h;
     if ((long)f.kernel_w * f.kernel_h > kNarrowCells || extent > kLong) return false;
     const double per_group = (double)f.beams / (double)f.groups;
     if (f.select >= LIDAR_ECHO_RAW_STRONGEST && per_group > 2.5) return false;
+    const bool shared = per_group > 1.01, one_pass = f.held_wave >= 8;
     double need = 2000.0;                                            // single beams
-    if (per_group > 1.01) {
-        if (f.held_wave >= 8) need = 3450.0 + 330.0 * per_group;
+    if (f.range_mode == LIDAR_RANGE_INTERVAL) {
+        if (!one_pass || per_group > 2.5 || extent > kRound) return false;
+        need = shared ? 6500.0 : 2500.0;
+    } else if (shared) {
+        if (one_pass) need = 3450.0 + 330.0 * per_group;
         else if (f.held > f.held_wave) need = 5000.0 + 900.0 * per_group;
         else need = 3500.0 + 1000.0 * per_group;
         if (extent > kRound) need += 2000.0;

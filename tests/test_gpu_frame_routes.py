@@ -63,7 +63,7 @@ def _beams(r, n, kernel, per_group):
     ("road", 9201, 1, 2048, 0, 0.03, "table", True),
     ("iid", 30404, 4, 400, 0, 0.03, "table", False),
 ])
-def test_wave_route(lidar, oracle_mod, scene, n, per_group, bins, select, sun, kernel, keep):
+def test_wave_route(lidar, oracle_mod, scene, n, per_group, bins, select, sun, kernel, keep, range_mode=0):
     import torch
     w = _scene(scene)
     r = w.gbuffer.raster
@@ -78,7 +78,7 @@ def test_wave_route(lidar, oracle_mod, scene, n, per_group, bins, select, sun, k
                              trunc_sigmas=3.0)
     span = w.params.n_bins * w.params.bin_ns
     params = replace(w.params, n_bins=bins, bin_ns=span / bins, echo_select=select, sun_irradiance=sun,
-                     sun_dir=(0.6, 0.0, 0.8))
+                     sun_dir=(0.6, 0.0, 0.8), range_mode=range_mode)
     planes = lidar.upload_gbuffer(w.gbuffer, "cuda")
     sim = lidar.LidarSim(params, stream=torch.cuda.current_stream(), keep_waveforms=keep)
     try:
@@ -94,10 +94,20 @@ def test_wave_route(lidar, oracle_mod, scene, n, per_group, bins, select, sun, k
         sim.close()
     assert (st["kernel_w"], st["kernel_h"]) == (2 * m + 1, 2 * k + 1)
     # (eight groups resident per CU at most: the strictest line)
-    assert routes.in_waves(n, info["n_items"], 2 * m + 1, 2 * k + 1, select, 0, 8, 8 if bins <= 512 else 4)
+    assert routes.in_waves(n, info["n_items"], 2 * m + 1, 2 * k + 1, select, range_mode, 8, 8 if bins <= 512 else 4)
     idx = np.unique(np.concatenate([np.arange(0, n, max(1, n // 1200)), np.arange(n - 40, n)]))
     part = replace(pat, beam_az=az[idx], beam_el=el[idx])
     ref = oracle_mod.simulate(w.gbuffer, part, params)
     got = {key: v[idx] if v is not None else None for key, v in got.items()}
     rep = (compare if select == 0 else compare_selection)(got, ref, params)
     assert rep.echoes_compared > 300 and rep.ambiguous < len(idx) // 4
+
+
+@pytest.mark.parametrize("scene,n,per_group,bins,select,sun,kernel,keep", [
+    ("road", 3103, 1, 512, 0, 0.0, "narrow", False),
+    ("iid", 3103, 1, 400, 2, 0.03, "wide", True),
+    ("wall", 13103, 2, 512, 0, 0.03, "narrow", False),
+    ("road", 3103, 1, 511, 4, 0.0, "narrow", True),
+])
+def test_wave_route_of_range_intervals(lidar, oracle_mod, scene, n, per_group, bins, select, sun, kernel, keep):
+    test_wave_route(lidar, oracle_mod, scene, n, per_group, bins, select, sun, kernel, keep, range_mode=2)

@@ -36,7 +36,14 @@ def test_a_kernel_writes_only_memory_of_the_one_device():
     ((8196, 4320, 7, 7, 0, 0, 8, 8), True),           # pairs
     ((13500, 7400, 9, 9, 0, 0, 7, 4), True),
     ((19500, 4920, 11, 11, 0, 0, 8, 8), True),        # full groups
+    ((3000, 3000, 9, 9, 2, 2, 8, 8), True),           # range intervals, one pass
+    ((9000, 7200, 11, 11, 0, 2, 8, 8), True),
     # each of these was slower by the wave (1.06 to 2.6 times)
+    ((2300, 2300, 9, 9, 0, 2, 8, 8), False),
+    ((6500, 5500, 13, 11, 0, 2, 8, 8), False),
+    ((24000, 6600, 9, 9, 0, 2, 8, 8), False),
+    ((9000, 9000, 15, 3, 0, 2, 8, 8), False),
+    ((9000, 9000, 9, 9, 0, 1, 8, 8), False),          # corrected ranges have a kernel of their own
     ((1256, 1256, 9, 9, 4, 0, 8, 8), False),
     ((3900, 3250, 5, 5, 0, 0, 7, 4), False),
     ((26000, 6624, 9, 9, 4, 0, 8, 8), False),         # full groups, raw selection
