@@ -40,10 +40,10 @@ inline bool one_device(int memory, int handle, int current)
 // without sun, kept waveforms and raw selection.  Against the groups the first
 // take 0.91 of the time on average (0.99 with every frame of 2048 beams in waves,
 // 2.2 at most there) and 1.04 at most, the second 0.80 and 1.17 at most; 2432
-// single beams of an 11 x 11 kernel 33.1 and 25.7 us.  What loses is shared groups on i.i.d. surfaces with 2048 bins, where every pixel ends a
-// run: at random places 0.92 to 1.35 (kept waveforms), where the road takes 0.62 to
-// 0.90 and the wall 0.59 to 0.83.  Left to the groups, with their times (groups,
-// waves):
+// single beams of an 11 x 11 kernel 33.1 and 25.7 us.  What loses is shared groups
+// on i.i.d. surfaces with 2048 bins, where every pixel ends a run: at random places
+// 0.92 to 1.35 (kept waveforms), where the road takes 0.62 to 0.90 and the wall 0.59
+// to 0.83.  Left to the groups, with their times (groups, waves):
 //  * few groups: 2048 beams of a 9 x 7 kernel in 1978 groups 24.6 and 36.9 us;
 //  * full groups: 24000 beams of a 9 x 7 kernel in 6000 groups (2048 bins) 1.09 of
 //    the time; raw selections, whose waveforms are not convolved, 0.74 to 1.40
